@@ -245,6 +245,20 @@ int hwave_query(hwave_table* t, const void* d_keys, uint64_t n, void* d_vals_out
  * with HWAVE_F_NO_ERASE. */
 int hwave_erase(hwave_table* t, const void* d_keys, uint64_t n, uint8_t* d_found, void* stream);
 
+/* The same write calls with scratch memory, for bulk calls: operations are first
+ * grouped by bucket, so that a bucket's lock, tags and slots are touched once for
+ * all of them (hw_bulk.hpp).  Results are those of the plain calls (the order of a
+ * call's operations is free).  hwave_write_scratch: the bytes a call of n
+ * operations of kind `op` (INSERT, UPSERT with `combine`, or ERASE) can use, 0
+ * where grouping does not pay; the caller owns the memory (256-byte aligned,
+ * contents free) until the enqueued work completes.  Without scratch memory, or
+ * with less, a call is the plain call. */
+int hwave_write_scratch(const hwave_table* t, hwave_op op, uint64_t n, hwave_combine combine, uint64_t* bytes);
+int hwave_upsert_scratch(hwave_table* t, const void* d_keys, const void* d_vals, uint64_t n, hwave_combine combine,
+                         uint8_t* d_status, void* d_scratch, uint64_t scratch_bytes, void* stream);
+int hwave_erase_scratch(hwave_table* t, const void* d_keys, uint64_t n, uint8_t* d_found, void* d_scratch,
+                        uint64_t scratch_bytes, void* stream);
+
 /* One launch running a different operation per element (the paper runs all
  * operations of an aging iteration concurrently in one kernel, Section 6.5).
  * d_ops[i] is a hwave_op; upserts use `combine`; d_vals is read for inserts and

@@ -29,6 +29,7 @@ F_NO_ERASE = 2
 F_BSP = 4
 F_AGGREGATE = 8
 F_MERGE_MIXED = 16
+BULK_MIN_OPS = 2048  # calls below this, or below 1/32 of the table's slots, never use scratch memory
 
 
 class HashWaveError(RuntimeError):
@@ -118,6 +119,9 @@ def _bind(L):
         "hwave_upsert": (I, [P, P, P, U64, I, P, P]),
         "hwave_query": (I, [P, P, U64, P, P, P]),
         "hwave_erase": (I, [P, P, U64, P, P]),
+        "hwave_write_scratch": (I, [P, I, U64, I, ctypes.POINTER(U64)]),
+        "hwave_upsert_scratch": (I, [P, P, P, U64, I, P, P, U64, P]),
+        "hwave_erase_scratch": (I, [P, P, U64, P, P, U64, P]),
         "hwave_mixed": (I, [P, P, P, P, U64, I, P, P, P]),
         "hwave_mixed_noalloc": (I, [P, P, P, P, U64, I, P, P, P]),
         "hwave_size": (I, [P, P, P]),
@@ -245,6 +249,33 @@ class Table:
             raise HashWaveError("keys/values must be contiguous %s tensors on %s" % (self.dtype, self.device))
         return t
 
+    def _scratch(self, op, n, combine, stream):
+        """Scratch memory of a bulk write (hwave_write_scratch), or None for the plain
+        call.  It comes from torch's allocator on the call's own stream, so it may be
+        released as soon as the call is enqueued, and it goes back with
+        torch.cuda.empty_cache().  A call that is being captured into a graph, whose
+        replays would outlive it, runs without, and so does one without room for it."""
+        if n < BULK_MIN_OPS or n < self.capacity >> 5:
+            return None
+        import torch
+        need = ctypes.c_uint64()
+        _check(self._L.hwave_write_scratch(self.h, op, n, combine, ctypes.byref(need)))
+        if not need.value:
+            return None
+        if stream is not None:
+            with torch.cuda.stream(torch.cuda.ExternalStream(stream.cuda_stream, device=self.device)):
+                return self._scratch_bytes(int(need.value))
+        return self._scratch_bytes(int(need.value))
+
+    def _scratch_bytes(self, n):
+        import torch
+        if torch.cuda.is_current_stream_capturing():
+            return None
+        try:
+            return torch.empty(n, dtype=torch.uint8, device=self.device)
+        except torch.cuda.OutOfMemoryError:
+            return None
+
     # -- operations (asynchronous on the current or given stream)
     def clear(self, stream=None):
         _check(self._L.hwave_clear(self.h, _stream(stream)))
@@ -252,6 +283,11 @@ class Table:
     def insert(self, keys, vals, status=None, stream=None):
         n = keys.numel()
         status = self._u8(n) if status is None else status
+        scratch = self._scratch(OPS["insert"], n, 1, stream)
+        if scratch is not None:
+            _check(self._L.hwave_upsert_scratch(self.h, _ptr(self._keys(keys)), _ptr(self._keys(vals)), n, 1,
+                                                _ptr(status), _ptr(scratch), scratch.numel(), _stream(stream)))
+            return status
         _check(self._L.hwave_insert(self.h, _ptr(self._keys(keys)), _ptr(self._keys(vals)), n,
                                   _ptr(status), _stream(stream)))
         return status
@@ -259,6 +295,12 @@ class Table:
     def upsert(self, keys, vals, combine="sum", status=None, stream=None):
         n = keys.numel()
         status = self._u8(n) if status is None else status
+        scratch = self._scratch(OPS["upsert"], n, COMBINES[combine], stream)
+        if scratch is not None:
+            _check(self._L.hwave_upsert_scratch(self.h, _ptr(self._keys(keys)), _ptr(self._keys(vals)), n,
+                                                COMBINES[combine], _ptr(status), _ptr(scratch), scratch.numel(),
+                                                _stream(stream)))
+            return status
         _check(self._L.hwave_upsert(self.h, _ptr(self._keys(keys)), _ptr(self._keys(vals)), n,
                                   COMBINES[combine], _ptr(status), _stream(stream)))
         return status
@@ -274,6 +316,11 @@ class Table:
     def erase(self, keys, found=None, stream=None):
         n = keys.numel()
         found = self._u8(n) if found is None else found
+        scratch = self._scratch(OPS["erase"], n, 0, stream)
+        if scratch is not None:
+            _check(self._L.hwave_erase_scratch(self.h, _ptr(self._keys(keys)), n, _ptr(found), _ptr(scratch),
+                                               scratch.numel(), _stream(stream)))
+            return found
         _check(self._L.hwave_erase(self.h, _ptr(self._keys(keys)), n, _ptr(found), _stream(stream)))
         return found
 

@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstring>
 #include <mutex>
 #include <vector>
@@ -386,6 +387,125 @@ int init_table(hwave_table* t, void* base, uint64_t bytes, const Layout& L, hwav
 
 bool bad_ptr(const void* p) { return p == nullptr; }
 
+// Most operations grouped in one go: larger calls run in equal pieces, so the
+// scratch memory stays bounded (about 50 bytes per operation).
+constexpr uint64_t BULK_CHUNK = 1ull << 27;
+
+// Blocks of k_bulk_write at work at a time: six a CU.
+constexpr uint64_t BULK_RESIDENT = 1536;
+
+// Room for a bin that receives `mean` operations on average: seven standard
+// deviations of a random spread; keys that are spread worse overflow into the
+// per-tile path.
+uint32_t bulk_room(double mean) { return (uint32_t)round_up((uint64_t)(mean + 7 * std::sqrt(mean)) + 32, 64); }
+
+// Fewest operations per home slot for which a call is grouped, in percent.  Plain
+// against grouped, microseconds, tables of 2^18 and 2^25 slots filled to 0.85,
+// upserts of present keys except where noted:
+//   tags:                0.11 per slot: ICEBERG_M 58 / 25; P2HT(M) erases of 0.125 142 / 54 (2^21), 708 /
+//                        312 (0.05: 32 / 29 and inserts 45 / 49)
+//   32-bit keys:         0.21: 56 / 26, 906 / 446; 0.11: 29 / 26, inserts 44 / 44
+//   64-bit, no tags:     DOUBLE 0.43: 56 / 31, 3581 / 1826 (0.85); 0.21: 42 / 29, inserts 52 / 53;
+//                        ICEBERG 0.21: 115 / 43 (2^19), 1485 / 630; P2HT erases of 0.125 96 / 89
+//                        (2^21), 233 / 238 (2^23)
+//   chaining, upserts:   whole chains are walked under the lock by one tile: 0.74: 74 / 44, 0.37:
+//                        44 / 34, inserts 51 / 46 (2^18) and 66 / 75 (2^19); erases go in parallel
+uint64_t bulk_min_percent(const hwave_table* t, bool erase) {
+  if (design_tags(t->design)) return 10;
+  if (design_chain(t->design)) return erase ? 25 : 60;
+  if (t->cfg.kv_bits == 32) return 16;
+  return t->design == HWAVE_ICEBERG ? 12 : 25;
+}
+
+// How a call of n operations (at most BULK_CHUNK) is grouped (hw_bulk.hpp), or
+// false where one tile per operation is better.
+bool bulk_plan(const hwave_table* t, uint64_t n, bool erase, BulkPlan* p) {
+  if (!(erase ? t->ks->bulk_erase : t->ks->bulk_upsert) || n < BULK_MIN_OPS) return false;
+  const uint32_t B = design_chain(t->design) ? 8 : t->cfg.bucket_slots;
+  const uint64_t nbh = t->la.tv.nb_front;  // home buckets
+  if (nbh == 0 || n * 100 < nbh * B * bulk_min_percent(t, erase)) return false;
+  const double per_bucket = (double)n / (double)nbh;
+  uint32_t shift = 0;
+  while ((2u << shift) * B <= (uint32_t)t->ks->bulk_slots) ++shift;
+  auto fits = [&](uint32_t sh) { return bulk_room(per_bucket * (double)(1u << sh)) <= (uint32_t)BULK_CAP; };
+  // as many buckets as a block takes, but enough blocks to fill the chip
+  while (shift > 0 && (!fits(shift) || (((nbh - 1) >> shift) + 1 < 512 && per_bucket * (double)(1u << shift) > 256))) --shift;
+  if (!fits(shift)) return false;
+  p->shift = shift;
+  p->parts = (uint32_t)(((nbh - 1) >> shift) + 1);
+  const double mean = per_bucket * (double)(1u << shift);
+  p->cap = bulk_room(mean);
+  p->hash_n = 256;
+  while (p->hash_n * 2 < p->cap * 3) p->hash_n *= 2;
+  // Iceberg inserts: no more tiles choose between two backyard buckets at a time than
+  // there are backyard buckets, as in a plain call, where such choices are spread
+  // over the call's time.  All at once they meet equal fills and take the first choice
+  // (a fill of 2^20 slots to 0.9: 2.89 lines per query, not 2.96), and the fills are a little
+  // less even.  That fill takes 364 us, 221 without the limit, 870 with half the
+  // tiles, 590 plain; 2^22 slots 446, 377, 620, 1182.
+  p->slow_tiles = BULK_THREADS;
+  if (!erase && design_iceberg(t->design))
+    p->slow_tiles = (uint32_t)std::min<uint64_t>(BULK_THREADS, t->la.tv.nb_back / std::min<uint64_t>(p->parts, BULK_RESIDENT) + 1);
+  p->sub = 0;
+  p->levels = p->parts <= (uint32_t)BULK_BINS ? 1 : 2;
+  if (p->levels == 2) {
+    while ((1u << (2 * p->sub)) < p->parts) ++p->sub;  // both levels about the square root
+    p->bins = ((p->parts - 1) >> p->sub) + 1;
+    p->cap1 = bulk_room(mean * (double)(1u << p->sub));
+  } else {
+    p->bins = p->parts;
+    p->cap1 = p->cap;
+  }
+  if ((1u << p->sub) > (uint32_t)BULK_BINS) return false;
+  const uint64_t pair = t->cfg.kv_bits / 8 * (erase ? 1 : 2);
+  const uint64_t room1 = (uint64_t)p->bins * p->cap1, room = p->levels == 2 ? (uint64_t)p->parts * p->cap : 0;
+  uint64_t off = 0;
+  auto place = [&](uint64_t bytes) {
+    const uint64_t at = off;
+    off += round_up(bytes, ALIGN);
+    return at;
+  };
+  p->off_cursor1 = place((uint64_t)p->bins * BULK_CSTRIDE * 4);
+  p->off_cursor = place(p->levels == 2 ? (uint64_t)p->parts * 4 : 0);
+  p->zero_bytes = off;
+  p->off_pos1 = place(n * 4);
+  p->off_pos = place(p->levels == 2 ? room1 * 4 : 0);
+  p->off_rec1 = place(room1 * pair);
+  p->off_rec = place(room * pair);
+  p->off_stat1 = place(room1);
+  p->off_stat = place(room);
+  p->bytes = off;
+  return room1 < 0xFFFFFFFFull && room < 0xFFFFFFFFull;
+}
+
+// Operations per piece of a grouped call, all pieces but the last of the same size.
+uint64_t bulk_piece(uint64_t n) {
+  const uint64_t pieces = (n + BULK_CHUNK - 1) / BULK_CHUNK;
+  return (n + pieces - 1) / pieces;
+}
+
+bool upsert_groups(const hwave_table* t, int combine) {
+  // tables that merge duplicates keep their own path for what it merges
+  return !(t->la.tv.aggregate && combine != HWAVE_REPLACE);
+}
+
+// A grouped call, piece by piece; false (nothing enqueued) where the call is not
+// grouped or the scratch memory does not hold it.
+bool bulk_run(hwave_table* t, bool erase, const void* keys, const void* vals, uint64_t n, int combine, uint8_t* status,
+              void* scratch, uint64_t scratch_bytes, hipStream_t s, hipError_t* err) {
+  BulkPlan p;
+  const uint64_t piece = bulk_piece(n), w = t->cfg.kv_bits / 8;
+  if (!scratch || ((uintptr_t)scratch % ALIGN) || !bulk_plan(t, piece, erase, &p) || p.bytes > scratch_bytes) return false;
+  *err = hipSuccess;
+  for (uint64_t at = 0; at < n && *err == hipSuccess; at += piece) {
+    const uint64_t m = n - at < piece ? n - at : piece;
+    *err = (erase ? t->ks->bulk_erase : t->ks->bulk_upsert)(
+        t->la, p, (uint8_t*)scratch, (const uint8_t*)keys + at * w, vals ? (const uint8_t*)vals + at * w : nullptr,
+        (uint32_t)m, combine, status ? status + at : nullptr, s);
+  }
+  return true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -505,6 +625,39 @@ int hwave_upsert(hwave_table* t, const void* d_keys, const void* d_vals, uint64_
   if (bad_ptr(d_keys) || bad_ptr(d_vals)) return HWAVE_EINVAL;
   hipError_t e = t->ks->upsert(t->la, d_keys, d_vals, n, (int)combine, d_status, (hipStream_t)stream);
   return e == hipSuccess ? HWAVE_OK : hip_fail(e);
+}
+
+int hwave_write_scratch(const hwave_table* t, hwave_op op, uint64_t n, hwave_combine combine, uint64_t* bytes) {
+  if (!t || !bytes || (int)op < HWAVE_OP_INSERT || (int)op > HWAVE_OP_ERASE) return HWAVE_EINVAL;
+  BulkPlan p;
+  const bool erase = op == HWAVE_OP_ERASE;
+  const bool grouped = n != 0 && (erase || upsert_groups(t, op == HWAVE_OP_INSERT ? (int)HWAVE_KEEP : (int)combine)) &&
+                       bulk_plan(t, bulk_piece(n), erase, &p);
+  *bytes = grouped ? p.bytes : 0;
+  return HWAVE_OK;
+}
+
+int hwave_upsert_scratch(hwave_table* t, const void* d_keys, const void* d_vals, uint64_t n, hwave_combine combine,
+                         uint8_t* d_status, void* d_scratch, uint64_t scratch_bytes, void* stream) {
+  if (!t || (int)combine < HWAVE_SUM || (int)combine > HWAVE_MAX) return HWAVE_EINVAL;
+  if (n == 0) return HWAVE_OK;
+  if (bad_ptr(d_keys) || bad_ptr(d_vals)) return HWAVE_EINVAL;
+  hipError_t e;
+  if (upsert_groups(t, (int)combine) && bulk_run(t, false, d_keys, d_vals, n, (int)combine, d_status, d_scratch,
+                                                 scratch_bytes, (hipStream_t)stream, &e))
+    return e == hipSuccess ? HWAVE_OK : hip_fail(e);
+  return hwave_upsert(t, d_keys, d_vals, n, combine, d_status, stream);
+}
+
+int hwave_erase_scratch(hwave_table* t, const void* d_keys, uint64_t n, uint8_t* d_found, void* d_scratch,
+                        uint64_t scratch_bytes, void* stream) {
+  if (!t || t->la.tv.no_erase) return HWAVE_EINVAL;
+  if (n == 0) return HWAVE_OK;
+  if (bad_ptr(d_keys)) return HWAVE_EINVAL;
+  hipError_t e;
+  if (bulk_run(t, true, d_keys, nullptr, n, HWAVE_KEEP, d_found, d_scratch, scratch_bytes, (hipStream_t)stream, &e))
+    return e == hipSuccess ? HWAVE_OK : hip_fail(e);
+  return hwave_erase(t, d_keys, n, d_found, stream);
 }
 
 int hwave_query(hwave_table* t, const void* d_keys, uint64_t n, void* d_vals_out, uint8_t* d_found,

@@ -40,13 +40,6 @@ __device__ __forceinline__ bool agg_merges(int combine) {
   return combine == C_SUM || combine == C_KEEP || combine == C_MIN || combine == C_MAX;
 }
 
-// Orders this wave's LDS accesses before the ones after it (all lanes).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <typename K>
 __device__ __forceinline__ K agg_identity(int combine) {
   return combine == C_MIN ? (K)~(K)0 : (K)0;

@@ -123,6 +123,13 @@ struct Tile {
   __device__ __forceinline__ bool leader() const { return tl == 0; }
 };
 
+// Orders this wave's LDS accesses before the ones after it (all lanes).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ int ffs64(uint64_t m) { return __ffsll((unsigned long long)m) - 1; }
 
 // ------------------------------------------------------------------ coherent access
@@ -146,14 +153,18 @@ __device__ __forceinline__ u32x4 ld16(const void* p) {
 // 16-byte agent-coherent store (one global_store_dwordx4 with the sc1 policy):
 // publishes a whole (key, value) slot in one request, the counterpart of the
 // paper's 128-bit release store (Section 4.2).  Completion is awaited by the
-// caller's next wait_mem().
+// caller's next wait_mem().  The s_nop gives the two wait states that a store of
+// more than 8 bytes needs on this chip before a vector instruction may overwrite
+// its data registers; the compiler inserts them after its own stores, but not
+// after one in inline assembly (without them, and with one, slots were published
+// with a register's next content).
 __device__ __forceinline__ void st16(void* p, uint64_t lo, uint64_t hi) {
   u32x4 v;
   v.x = (uint32_t)lo;
   v.y = (uint32_t)(lo >> 32);
   v.z = (uint32_t)hi;
   v.w = (uint32_t)(hi >> 32);
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
 }
 
 template <typename X>
@@ -253,6 +264,17 @@ struct LockArray {
 
 __device__ __forceinline__ uint64_t lock_at(const LockArray& L, uint32_t b) { return (uint64_t)b << L.shift; }
 __device__ __forceinline__ uint32_t lock_pattern(uint64_t at) { return 1u << ((uint32_t)(at & 3u) * 8u); }
+
+// ORs `want`, a pattern over the lock bytes of the aligned 8 bytes that hold bucket
+// b's (the calling lane alone); returns them as they were.
+__device__ __forceinline__ uint64_t try_locks(const LockArray& L, uint32_t b, uint64_t want) {
+#ifdef HW_STRICT_ORDER
+  constexpr int order = __ATOMIC_ACQUIRE;
+#else
+  constexpr int order = __ATOMIC_RELAXED;
+#endif
+  return __hip_atomic_fetch_or((uint64_t*)L.words + (lock_at(L, b) >> 3), want, order, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Leader lane ORs bucket b's lock byte; every lane learns whether it was clear
 // (then the tile holds the lock).

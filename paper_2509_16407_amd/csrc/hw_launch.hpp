@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include "hw_agg.hpp"
+#include "hw_bulk.hpp"
 #include "hw_merge.hpp"
 #include "hw_ops.hpp"
 
@@ -258,6 +259,9 @@ typedef hipError_t (*erase_fn)(const LaunchArgs&, const void*, uint64_t, uint8_t
 typedef hipError_t (*mixed_fn)(const LaunchArgs&, const uint8_t*, const void*, const void*, uint64_t,
                                int, void*, uint8_t*, const MergeWs*, hipStream_t);
 
+typedef hipError_t (*bulk_fn)(const LaunchArgs&, const BulkPlan&, uint8_t*, const void*, const void*, uint32_t, int,
+                              uint8_t*, hipStream_t);
+
 struct KernelSet {
   int kv_bits, design, bucket, tile;
   bool bsp;  // phased variant (no locks, plain loads in queries)
@@ -265,6 +269,8 @@ struct KernelSet {
   query_fn query;
   erase_fn erase;
   mixed_fn mixed;
+  int bulk_slots;  // most slots per part of a grouped call
+  bulk_fn bulk_upsert, bulk_erase;  // grouped by bucket (hw_bulk.hpp); null: the design has no such form
 };
 
 template <class C>
@@ -296,6 +302,57 @@ struct Launch {
                        (const K*)keys, n, found);
     return hipGetLastError();
   }
+  // One grouped call (hw_bulk.hpp) over n operations, in the scratch memory the
+  // plan was made for.
+  template <bool ERASE>
+  static hipError_t bulk(const LaunchArgs& a, const BulkPlan& p, uint8_t* scratch, const void* keys, const void* vals,
+                         uint32_t n, int combine, uint8_t* status, hipStream_t s) {
+    const HomeMap home{a.tv.bucket_mask, C::CHAIN || C::ICEBERG ? a.tv.nb_front : 0u};
+    uint32_t* cursor1 = (uint32_t*)(scratch + p.off_cursor1);
+    uint32_t* pos1 = (uint32_t*)(scratch + p.off_pos1);
+    K* rec1 = (K*)(scratch + p.off_rec1);
+    uint8_t* stat1 = scratch + p.off_stat1;
+    hipLaunchKernelGGL((k_bulk_zero<K>), dim3((unsigned)((p.zero_bytes / 16 + 255) / 256)), dim3(256), 0, s, (uint4*)cursor1,
+                       (uint32_t)(p.zero_bytes / 16), ERASE && !C::DOUBLE ? a.tv.ctrl : nullptr);
+    const uint32_t shift1 = p.shift + (p.levels == 2 ? p.sub : 0);
+    if (n >= BULK_WIDE_TILE) split<ERASE, false, 8>(p.bins, s, keys, vals, n, n, nullptr, home, shift1, 0, p.cap1, cursor1, BULK_CSTRIDE, rec1, pos1);
+    else split<ERASE, false, 4>(p.bins, s, keys, vals, n, n, nullptr, home, shift1, 0, p.cap1, cursor1, BULK_CSTRIDE, rec1, pos1);
+    const unsigned grid = grid_for((n + 63) / 64, 64, a.max_blocks);
+    const K* v = (const K*)vals;
+    BulkLds<C, ERASE> L;
+    const uint32_t lds = L.place(nullptr, p.cap, p.hash_n, 1u << p.shift);
+    auto write = [&](const K* rec, const uint32_t* cursor, uint32_t cstride, uint8_t* stat) {
+      hipLaunchKernelGGL((k_bulk_write<C, ERASE>), dim3(p.parts), dim3(BULK_THREADS), lds, s, a.tv, rec, cursor, cstride,
+                         p.cap, p.hash_n, p.shift, std::min<uint32_t>(p.slow_tiles, BULK_THREADS / C::T), combine, stat);
+    };
+    if (p.levels == 1) {
+      write(rec1, cursor1, BULK_CSTRIDE, stat1);
+    } else {
+      uint32_t* cursor = (uint32_t*)(scratch + p.off_cursor);
+      uint32_t* pos = (uint32_t*)(scratch + p.off_pos);
+      K* rec = (K*)(scratch + p.off_rec);
+      uint8_t* stat = scratch + p.off_stat;
+      split<ERASE, true, 8>(1u << p.sub, s, rec1, nullptr, p.bins * p.cap1, p.cap1, cursor1, home, p.shift, p.sub, p.cap,
+                            cursor, 1, rec, pos);
+      write(rec, cursor, 1, stat);
+      hipLaunchKernelGGL((k_bulk_back<K>), dim3(grid), dim3(256), 0, s, p.bins, p.cap1, cursor1, pos, stat, stat1);
+    }
+    hipLaunchKernelGGL((k_bulk_finish<C, ERASE>), dim3(grid), dim3(BLOCK), 0, s, a.tv, (const K*)keys,
+                       ERASE ? (const K*)keys : v, n, pos1, stat1, combine, status);
+    return hipGetLastError();
+  }
+  // One level of the split; REC: from the regions of the level before.
+  template <bool ERASE, bool REC, int PER>
+  static void split(uint32_t bins, hipStream_t s, const void* keys, const void* vals, uint32_t n, uint32_t region_cap,
+                    const uint32_t* region_count, const HomeMap& home, uint32_t shift, uint32_t bins_log2, uint32_t cap,
+                    uint32_t* cursor, uint32_t cstride, K* rec, uint32_t* pos) {
+    constexpr uint32_t TILE = BULK_SPLIT_THREADS * PER;
+    const uint32_t tiles = (region_cap + TILE - 1) / TILE;
+    hipLaunchKernelGGL((k_bulk_split<K, !ERASE, REC, PER>), dim3(n / region_cap * tiles), dim3(BULK_SPLIT_THREADS), 0, s,
+                       (const K*)keys, (const K*)vals, n, region_cap, region_count, home, shift, bins_log2, bins, cap,
+                       cursor, cstride, rec, pos);
+  }
+
   // One kernel launch of the mixed kernel over ops [0, n).
   template <bool MERGED>
   static void mixed_launch(const LaunchArgs& a, const uint8_t* ops, const K* keys, const K* vals, uint64_t n,
@@ -342,10 +399,23 @@ struct Launch {
   }
 };
 
+// Cuckoo operations hold three buckets, the phased variant no lock, and a bucket
+// of more than 64 slots has no free-slot mask: those stay with one tile per operation.
+// So do inserts into two-choice tables: there a key's bucket is chosen by the fills of
+// the moment, and a part works on all of its buckets' operations while other buckets'
+// are yet to come, so that fills say little.  A fill of 2^28 slots to 0.9 left
+// thousands of keys FULL (one by one: none); parts that filled buckets to 3/4 only, in
+// small pieces, left none, but gained little (0.7 to 1.5 times the plain rate).
+template <class C, bool ERASE>
+constexpr bulk_fn bulk_of() {
+  if constexpr (!C::CUCKOO && !C::BSP && C::B <= 64 && (ERASE || (C::DESIGN != D_P2 && C::DESIGN != D_P2_M))) return &Launch<C>::template bulk<ERASE>;
+  else return nullptr;
+}
+
 template <class C>
 constexpr KernelSet make_set() {
   return KernelSet{(int)sizeof(typename C::K) * 8, C::DESIGN, C::B, C::T, C::BSP, &Launch<C>::upsert,
-                   &Launch<C>::query, &Launch<C>::erase, &Launch<C>::mixed};
+                   &Launch<C>::query, &Launch<C>::erase, &Launch<C>::mixed, bulk_slots<C>(), bulk_of<C, false>(), bulk_of<C, true>()};
 }
 
 // Instance tables, one per translation unit.

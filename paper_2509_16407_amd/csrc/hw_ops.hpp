@@ -427,15 +427,16 @@ struct Ops {
   // Upsert callback applied to a present key (Section 5.1).
   __device__ static void combine_at(const TableDev& tv, const Tile<T>& tile, uint64_t s, K val,
                                     int combine) {
-    if (tile.leader()) {
-      K* vp = val_ptr(tv, s);
-      switch (combine) {
-        case C_SUM: __hip_atomic_fetch_add(vp, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break;
-        case C_REPLACE: st(vp, val); break;
-        case C_MIN: __hip_atomic_fetch_min(vp, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break;
-        case C_MAX: __hip_atomic_fetch_max(vp, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break;
-        default: break;
-      }
+    if (tile.leader()) combine_lane(tv, s, val, combine);
+  }
+  __device__ static __forceinline__ void combine_lane(const TableDev& tv, uint64_t s, K val, int combine) {
+    K* vp = val_ptr(tv, s);
+    switch (combine) {
+      case C_SUM: __hip_atomic_fetch_add(vp, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break;
+      case C_REPLACE: st(vp, val); break;
+      case C_MIN: __hip_atomic_fetch_min(vp, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break;
+      case C_MAX: __hip_atomic_fetch_max(vp, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break;
+      default: break;
     }
   }
 
@@ -491,6 +492,15 @@ struct Ops {
       const Hashed h = hash_key((uint64_t)key, tv.bucket_mask);
       return Home{h.b1, h.h2, 0u};
     }
+  }
+
+  // The buckets that are some key's home (b1), and the home bucket of the key
+  // whose salted mix is h.
+  __device__ static __forceinline__ uint32_t home_buckets(const TableDev& tv) {
+    return C::CHAIN || C::ICEBERG ? tv.nb_front : tv.bucket_mask + 1;
+  }
+  __device__ static __forceinline__ uint32_t home_of_hash(const TableDev& tv, uint64_t h) {
+    return C::CHAIN || C::ICEBERG ? __umulhi((uint32_t)h, tv.nb_front) : (uint32_t)h & tv.bucket_mask;
   }
 
   // The erase flag, read by the leader and broadcast.
@@ -1035,12 +1045,7 @@ struct Ops {
     // two writers of one chain (only its queries differ, Table 1's phased column).
     if constexpr (C::BSP && !C::CHAIN) {
       if (erase) return erase_locked(tv, tile, h, key, tag);
-      if constexpr (C::ICEBERG)
-        return upsert_iceberg_locked(tv, tile, h, key, val, tag, combine);
-      else if constexpr (C::DOUBLE)
-        return upsert_double_locked(tv, tile, h, key, val, tag, combine);
-      else
-        return upsert_p2_locked(tv, tile, h, key, val, tag, combine);
+      return upsert_locked(tv, tile, h, key, val, tag, combine);
     }
     if (!erase && tv.no_erase) {
       K cur;
@@ -1056,15 +1061,23 @@ struct Ops {
     }
     return locked(tv, tile, h.b1, [&]() -> uint8_t {
       if (erase) return erase_locked(tv, tile, h, key, tag);
-      if constexpr (C::CHAIN)
-        return upsert_chain_locked(tv, tile, h, key, val, combine);
-      else if constexpr (C::ICEBERG)
-        return upsert_iceberg_locked(tv, tile, h, key, val, tag, combine);
-      else if constexpr (C::DOUBLE)
-        return upsert_double_locked(tv, tile, h, key, val, tag, combine);
-      else
-        return upsert_p2_locked(tv, tile, h, key, val, tag, combine);
+      return upsert_locked(tv, tile, h, key, val, tag, combine);
     });
+  }
+
+  // Finds or inserts `key` under its home bucket's lock; `shared`: other tiles work
+  // under the same lock, on other keys (not in chains).
+  __device__ static __forceinline__ uint8_t upsert_locked(const TableDev& tv, const Tile<T>& tile, const Home& h,
+                                                          K key, K val, uint32_t tag, int combine,
+                                                          bool shared = false) {
+    if constexpr (C::CHAIN)
+      return upsert_chain_locked(tv, tile, h, key, val, combine);
+    else if constexpr (C::ICEBERG)
+      return upsert_iceberg_locked(tv, tile, h, key, val, tag, combine, !C::BSP && !shared);
+    else if constexpr (C::DOUBLE)
+      return upsert_double_locked(tv, tile, h, key, val, tag, combine);
+    else
+      return upsert_p2_locked(tv, tile, h, key, val, tag, combine);
   }
 
   __device__ static uint8_t upsert_double_locked(const TableDev& tv, const Tile<T>& tile,
@@ -1163,7 +1176,7 @@ struct Ops {
   // happened), else the less loaded backyard choice, ties to the first.
   __device__ static uint8_t upsert_iceberg_locked(const TableDev& tv, const Tile<T>& tile,
                                                   const Home& h, K key, K val, uint32_t tag,
-                                                  int combine) {
+                                                  int combine, bool excl) {
     if (tile.leader()) probe_add(tv, PC_WRITE, 1);
     BucketScan<K> rf = scan<true>(tv, tile, h.b1, key, tag);
     if (tile.leader()) probe_add(tv, PC_VISIT, 1);
@@ -1172,10 +1185,10 @@ struct Ops {
       return ST_EXISTED;
     }
     // Front-yard slots are claimed only under this lock: plain stores suffice
-    // (not in the phased variant, which takes no lock).
+    // (not in the phased variant, which takes no lock, nor where tiles share it).
     if (rf.free >= 0 && !erased(tv, tile)) {
-      if (claim_in_bucket(tv, tile, h.b1, rf, key, val, tag, !C::BSP) >= 0) return ST_DONE;
-      rf = scan<false>(tv, tile, h.b1, key, tag);  // phased variant: lost the slot to another key
+      if (claim_in_bucket(tv, tile, h.b1, rf, key, val, tag, excl) >= 0) return ST_DONE;
+      rf = scan<false>(tv, tile, h.b1, key, tag);  // (not excl) lost the slot to another key
     }
     BucketScan<K> r1 = scan<true>(tv, tile, h.h2, key, tag);
     if (tile.leader()) probe_add(tv, PC_VISIT, 1);
@@ -1192,7 +1205,7 @@ struct Ops {
         return ST_EXISTED;
       }
     }
-    if (rf.free >= 0 && claim_in_bucket(tv, tile, h.b1, rf, key, val, tag, !C::BSP) >= 0) return ST_DONE;
+    if (rf.free >= 0 && claim_in_bucket(tv, tile, h.b1, rf, key, val, tag, excl) >= 0) return ST_DONE;
     if (h.b3 == h.h2) return claim_in_bucket(tv, tile, h.h2, r1, key, val, tag) >= 0 ? ST_DONE : ST_FULL;
     return claim_less_loaded(tv, tile, h.h2, r1, h.b3, r2, key, val, tag);
   }
