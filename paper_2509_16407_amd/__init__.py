@@ -29,7 +29,7 @@ F_NO_ERASE = 2
 F_BSP = 4
 F_AGGREGATE = 8
 F_MERGE_MIXED = 16
-BULK_MIN_OPS = 2048  # calls below this, or below 1/32 of the table's slots, never use scratch memory
+BULK_MIN_OPS = 2048  # calls below this never use scratch memory
 
 
 class HashWaveError(RuntimeError):
@@ -141,6 +141,8 @@ def _bind(L):
         "hwave_multi_run": (I, [P, P, ctypes.c_uint32, P, P, P, P, P]),
         "hwave_multi_clear": (I, [P, P]),
         "hwave_multi_upsert": (I, [P, P, P, P, I, P, P]),
+        "hwave_multi_scratch": (I, [P, P, I, ctypes.POINTER(U64)]),
+        "hwave_multi_upsert_scratch": (I, [P, P, P, P, I, P, P, U64, P]),
         "hwave_multi_upsert_tables": (I, [P, ctypes.c_uint32, P, P, P, I, P, P]),
         "hwave_server_create": (I, [ctypes.POINTER(P), P, ctypes.c_uint32, ctypes.POINTER(_ServerCfg)]),
         "hwave_server_submit": (I, [P, ctypes.POINTER(_Request), ctypes.c_double, ctypes.POINTER(U64)]),
@@ -181,6 +183,21 @@ def _stream(stream):
     import torch
     s = stream if stream is not None else torch.cuda.current_stream()
     return ctypes.c_void_p(s.cuda_stream)
+
+
+def _scratch_memory(n, device, stream):
+    """n bytes from torch's allocator on the given stream; None without room for them, or
+    while the stream is being captured into a graph."""
+    import torch
+    if stream is not None:
+        with torch.cuda.stream(torch.cuda.ExternalStream(stream.cuda_stream, device=device)):
+            return _scratch_memory(n, device, None)
+    if torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(n, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
 
 
 class Table:
@@ -255,26 +272,13 @@ class Table:
         released as soon as the call is enqueued, and it goes back with
         torch.cuda.empty_cache().  A call that is being captured into a graph, whose
         replays would outlive it, runs without, and so does one without room for it."""
-        if n < BULK_MIN_OPS or n < self.capacity >> 5:
+        if n < BULK_MIN_OPS or n * 13 < self.capacity or (self.design in ("P2", "P2_M") and op != OPS["erase"]):
             return None
-        import torch
         need = ctypes.c_uint64()
         _check(self._L.hwave_write_scratch(self.h, op, n, combine, ctypes.byref(need)))
         if not need.value:
             return None
-        if stream is not None:
-            with torch.cuda.stream(torch.cuda.ExternalStream(stream.cuda_stream, device=self.device)):
-                return self._scratch_bytes(int(need.value))
-        return self._scratch_bytes(int(need.value))
-
-    def _scratch_bytes(self, n):
-        import torch
-        if torch.cuda.is_current_stream_capturing():
-            return None
-        try:
-            return torch.empty(n, dtype=torch.uint8, device=self.device)
-        except torch.cuda.OutOfMemoryError:
-            return None
+        return _scratch_memory(int(need.value), self.device, stream)
 
     # -- operations (asynchronous on the current or given stream)
     def clear(self, stream=None):
@@ -453,11 +457,25 @@ class Multi:
                                      _ptr(vals), _ptr(out), _ptr(status), _stream(stream)))
         return status, out
 
+    def _scratch(self, offs, n, combine, stream):
+        """Scratch memory of a bulk upsert (hwave_multi_scratch), as Table._scratch."""
+        if n < BULK_MIN_OPS or len(offs) != len(self.tables) + 1:
+            return None
+        need = ctypes.c_uint64()
+        _check(lib().hwave_multi_scratch(self.h, ctypes.cast(offs, ctypes.c_void_p), combine, ctypes.byref(need)))
+        return _scratch_memory(int(need.value), self.tables[0].device, stream) if need.value else None
+
     def upsert(self, offsets, keys, vals, combine="sum", status=None, stream=None):
         import torch
         n = keys.numel()
         status = torch.empty(n, dtype=torch.uint8, device=keys.device) if status is None else status
         offs = (ctypes.c_uint64 * len(offsets))(*[int(x) for x in offsets])
+        scratch = self._scratch(offs, n, COMBINES[combine], stream)
+        if scratch is not None:
+            _check(lib().hwave_multi_upsert_scratch(self.h, ctypes.cast(offs, ctypes.c_void_p), _ptr(keys), _ptr(vals),
+                                                    COMBINES[combine], _ptr(status), _ptr(scratch), scratch.numel(),
+                                                    _stream(stream)))
+            return status
         _check(lib().hwave_multi_upsert(self.h, ctypes.cast(offs, ctypes.c_void_p), _ptr(keys), _ptr(vals),
                                         COMBINES[combine], _ptr(status), _stream(stream)))
         return status

@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <vector>
 
 #include "hashwave.h"
@@ -439,6 +440,18 @@ constexpr uint64_t BULK_RESIDENT = 1536;
 // per-tile path.
 uint32_t bulk_room(double mean) { return (uint32_t)round_up((uint64_t)(mean + 7 * std::sqrt(mean)) + 32, 64); }
 
+// What a plan depends on.
+struct BulkShape {
+  const KernelSet* ks;
+  hwave_design design;
+  uint32_t kv_bits, B;  // B: slot units per home bucket
+  uint64_t nbh, backs;  // home buckets; iceberg's backyard buckets
+};
+BulkShape bulk_shape(const hwave_table* t) {
+  return BulkShape{t->ks, t->design, t->cfg.kv_bits, design_chain(t->design) ? 8u : t->cfg.bucket_slots,
+                   t->la.tv.nb_front, t->la.tv.nb_back};
+}
+
 // Fewest operations per home slot for which a call is grouped, in percent.  Plain
 // against grouped, microseconds, tables of 2^18 and 2^25 slots filled to 0.85,
 // upserts of present keys except where noted:
@@ -450,26 +463,28 @@ uint32_t bulk_room(double mean) { return (uint32_t)round_up((uint64_t)(mean + 7 
 //                        (2^21), 233 / 238 (2^23)
 //   chaining, upserts:   whole chains are walked under the lock by one tile: 0.74: 74 / 44, 0.37:
 //                        44 / 34, inserts 51 / 46 (2^18) and 66 / 75 (2^19); erases go in parallel
-uint64_t bulk_min_percent(const hwave_table* t, bool erase) {
-  if (design_tags(t->design)) return 10;
-  if (design_chain(t->design)) return erase ? 25 : 60;
-  if (t->cfg.kv_bits == 32) return 16;
-  return t->design == HWAVE_ICEBERG ? 12 : 25;
+uint64_t bulk_min_percent(const BulkShape& t, bool erase) {
+  if (design_tags(t.design)) return 10;
+  if (design_chain(t.design)) return erase ? 25 : 60;
+  if (t.kv_bits == 32) return 16;
+  return t.design == HWAVE_ICEBERG ? 12 : 25;
 }
 
 // How a call of n operations (at most BULK_CHUNK) is grouped (hw_bulk.hpp), or
-// false where one tile per operation is better.
-bool bulk_plan(const hwave_table* t, uint64_t n, bool erase, BulkPlan* p) {
-  if (!(erase ? t->ks->bulk_erase : t->ks->bulk_upsert) || n < BULK_MIN_OPS) return false;
-  const uint32_t B = design_chain(t->design) ? 8 : t->cfg.bucket_slots;
-  const uint64_t nbh = t->la.tv.nb_front;  // home buckets
+// false where one tile per operation is better.  `member`: as one of many tables of
+// a call, which fill the chip together.
+bool bulk_plan(const BulkShape& t, uint64_t n, bool erase, bool member, BulkPlan* p) {
+  if (!(erase ? t.ks->bulk_erase : t.ks->bulk_upsert) || n < (member ? 1 : BULK_MIN_OPS) || n > BULK_CHUNK) return false;
+  const uint32_t B = t.B;
+  const uint64_t nbh = t.nbh;
   if (nbh == 0 || n * 100 < nbh * B * bulk_min_percent(t, erase)) return false;
   const double per_bucket = (double)n / (double)nbh;
   uint32_t shift = 0;
-  while ((2u << shift) * B <= (uint32_t)t->ks->bulk_slots) ++shift;
+  while ((2u << shift) * B <= (uint32_t)t.ks->bulk_slots) ++shift;
   auto fits = [&](uint32_t sh) { return bulk_room(per_bucket * (double)(1u << sh)) <= (uint32_t)BULK_CAP; };
   // as many buckets as a block takes, but enough blocks to fill the chip
-  while (shift > 0 && (!fits(shift) || (((nbh - 1) >> shift) + 1 < 512 && per_bucket * (double)(1u << shift) > 256))) --shift;
+  while (shift > 0 && (!fits(shift) || (!member && ((nbh - 1) >> shift) + 1 < 512 && per_bucket * (double)(1u << shift) > 256)))
+    --shift;
   if (!fits(shift)) return false;
   p->shift = shift;
   p->parts = (uint32_t)(((nbh - 1) >> shift) + 1);
@@ -484,8 +499,8 @@ bool bulk_plan(const hwave_table* t, uint64_t n, bool erase, BulkPlan* p) {
   // less even.  That fill takes 364 us, 221 without the limit, 870 with half the
   // tiles, 590 plain; 2^22 slots 446, 377, 620, 1182.
   p->slow_tiles = BULK_THREADS;
-  if (!erase && design_iceberg(t->design))
-    p->slow_tiles = (uint32_t)std::min<uint64_t>(BULK_THREADS, t->la.tv.nb_back / std::min<uint64_t>(p->parts, BULK_RESIDENT) + 1);
+  if (!erase && design_iceberg(t.design))
+    p->slow_tiles = (uint32_t)std::min<uint64_t>(BULK_THREADS, t.backs / std::min<uint64_t>(p->parts, BULK_RESIDENT) + 1);
   p->sub = 0;
   p->levels = p->parts <= (uint32_t)BULK_BINS ? 1 : 2;
   if (p->levels == 2) {
@@ -497,7 +512,7 @@ bool bulk_plan(const hwave_table* t, uint64_t n, bool erase, BulkPlan* p) {
     p->cap1 = p->cap;
   }
   if ((1u << p->sub) > (uint32_t)BULK_BINS) return false;
-  const uint64_t pair = t->cfg.kv_bits / 8 * (erase ? 1 : 2);
+  const uint64_t pair = t.kv_bits / 8 * (erase ? 1 : 2);
   const uint64_t room1 = (uint64_t)p->bins * p->cap1, room = p->levels == 2 ? (uint64_t)p->parts * p->cap : 0;
   uint64_t off = 0;
   auto place = [&](uint64_t bytes) {
@@ -535,7 +550,7 @@ bool bulk_run(hwave_table* t, bool erase, const void* keys, const void* vals, ui
               void* scratch, uint64_t scratch_bytes, hipStream_t s, hipError_t* err) {
   BulkPlan p;
   const uint64_t piece = bulk_piece(n), w = t->cfg.kv_bits / 8;
-  if (!scratch || ((uintptr_t)scratch % ALIGN) || !bulk_plan(t, piece, erase, &p) || p.bytes > scratch_bytes) return false;
+  if (!scratch || ((uintptr_t)scratch % ALIGN) || !bulk_plan(bulk_shape(t), piece, erase, false, &p) || p.bytes > scratch_bytes) return false;
   *err = hipSuccess;
   for (uint64_t at = 0; at < n && *err == hipSuccess; at += piece) {
     const uint64_t m = n - at < piece ? n - at : piece;
@@ -672,7 +687,7 @@ int hwave_write_scratch(const hwave_table* t, hwave_op op, uint64_t n, hwave_com
   BulkPlan p;
   const bool erase = op == HWAVE_OP_ERASE;
   const bool grouped = n != 0 && (erase || upsert_groups(t, op == HWAVE_OP_INSERT ? (int)HWAVE_KEEP : (int)combine)) &&
-                       bulk_plan(t, bulk_piece(n), erase, &p);
+                       bulk_plan(bulk_shape(t), bulk_piece(n), erase, false, &p);
   *bytes = grouped ? p.bytes : 0;
   return HWAVE_OK;
 }
@@ -936,6 +951,8 @@ struct hwave_multi {
   bool agg;  // some table merges duplicate keys (64-bit solo kernels: the merging path)
   uint32_t n_tables;
   std::vector<uint64_t> table_bytes;  // footprint per table (queue placement)
+  std::vector<BulkShape> shapes;      // per table, for grouped upserts
+  std::vector<HomeMap> homes;
   MultiTable* d_tables = nullptr;
   uint32_t* d_heads = nullptr;
   uint32_t* d_hot = nullptr;  // indices of the tables with hot-key accumulators the kernel fills
@@ -1038,7 +1055,12 @@ int hwave_multi_create(hwave_multi** out, hwave_table* const* tables, uint32_t n
   m->agg = false;
   for (uint32_t i = 0; i < n_tables; i++) m->agg = m->agg || tables[i]->la.tv.aggregate;
   m->n_tables = n_tables;
-  for (uint32_t i = 0; i < n_tables; i++) m->table_bytes.push_back(tables[i]->bytes);
+  for (uint32_t i = 0; i < n_tables; i++) {
+    const TableDev& tv = tables[i]->la.tv;
+    m->table_bytes.push_back(tables[i]->bytes);
+    m->shapes.push_back(bulk_shape(tables[i]));
+    m->homes.push_back(HomeMap{tv.bucket_mask, design_iceberg(tables[i]->design) || design_chain(tables[i]->design) ? tv.nb_front : 0u});
+  }
   // only the 64-bit menu carries the merging path that fills the accumulators
   std::vector<uint32_t> hot;
   for (uint32_t i = 0; i < n_tables; i++)
@@ -1173,6 +1195,117 @@ int hwave_multi_upsert(hwave_multi* m, const uint64_t* h_offsets, const void* d_
                                h_offsets[i + 1]});
   }
   return hwave_multi_run(m, items.data(), (uint32_t)items.size(), d_keys, d_vals, nullptr, d_status, stream);
+}
+
+}  // extern "C"
+
+namespace {
+
+// A group's upsert, grouped by bucket (hw_bulk.hpp): the jobs and, per step, the blocks
+// before each job's.  False where one tile per operation is better: few operations, or
+// most of them in tables that get too few; and for tables of different configurations.
+//
+// One tile per operation against grouped, microseconds, 32-bit DOUBLE tables filled to
+// 0.85: 40 of 2^12 slots 360 / 65, 400 of 2^10 370 / 129, 4 of 2^20 658 / 216, 20 of 2^20 with 1.7
+// operations per slot 5125 / 1714; ICEBERG_M, 64-bit, 10 of 2^13 564 / 125, 20 of 2^20 5265 / 2041.
+bool group_plan(const hwave_multi* m, const uint64_t* offsets, int combine, std::vector<BulkJob>* jobs,
+                std::vector<uint32_t>* first, GroupArgs* a, uint64_t* bytes) try {
+  if (m->menu != MENU_SOLO || !m->shapes[0].ks->group_upsert || (m->agg && combine != HWAVE_REPLACE)) return false;
+  uint64_t total = 0, grouped = 0;
+  for (uint32_t i = 0; i < m->n_tables; i++) {
+    if (offsets[i + 1] < offsets[i]) return false;
+    total += offsets[i + 1] - offsets[i];
+  }
+  if (total < BULK_MIN_OPS || total > 0xFFFFFFFFull) return false;
+  for (uint32_t i = 0; i < m->n_tables; i++) {
+    BulkJob j{};
+    j.home = m->homes[i];
+    j.table = i;
+    j.n = (uint32_t)(offsets[i + 1] - offsets[i]);
+    j.begin = offsets[i];
+    if (j.n == 0) continue;
+    if (bulk_plan(m->shapes[i], j.n, false, true, &j.plan)) grouped += j.n;
+    else j.plan = BulkPlan{};
+    jobs->push_back(j);
+  }
+  if (2 * grouped < total) return false;
+  const uint32_t n = (uint32_t)jobs->size();
+  first->assign((size_t)GROUP_STEPS * n, 0);
+  uint64_t at = round_up(n * sizeof(BulkJob), ALIGN) + round_up(first->size() * 4, ALIGN);
+  uint64_t blocks[GROUP_STEPS] = {};
+  constexpr uint64_t TILE = (uint64_t)BULK_SPLIT_THREADS * GROUP_PER;
+  for (uint32_t i = 0; i < n; i++) {
+    BulkJob& j = (*jobs)[i];
+    const BulkPlan& p = j.plan;
+    const bool on = p.levels != 0, two = p.levels == 2;
+    const uint64_t step[GROUP_STEPS] = {on ? (p.zero_bytes + GROUP_ZERO_BYTES - 1) / GROUP_ZERO_BYTES : 0,
+                                        on ? (j.n + TILE - 1) / TILE : 0,
+                                        two ? p.bins * ((p.cap1 + TILE - 1) / TILE) : 0,
+                                        on ? p.parts : 0,
+                                        two ? (uint64_t)p.bins * ((p.cap1 + 255) / 256) : 0,
+                                        ((uint64_t)j.n + GROUP_FINISH_OPS - 1) / GROUP_FINISH_OPS};
+    for (int k = 0; k < GROUP_STEPS; k++) {
+      (*first)[(size_t)k * n + i] = (uint32_t)blocks[k];
+      blocks[k] += step[k];
+    }
+    j.scratch = at;
+    at += p.bytes;
+  }
+  for (int k = 0; k < GROUP_STEPS; k++) {
+    if (blocks[k] > 0x7FFFFFFFull) return false;
+    a->blocks[k] = (uint32_t)blocks[k];
+  }
+  a->n = total;
+  *bytes = at;
+  return true;
+} catch (const std::bad_alloc&) {
+  return false;
+}
+
+}  // namespace
+
+extern "C" {
+
+int hwave_multi_scratch(const hwave_multi* m, const uint64_t* h_offsets, hwave_combine combine, uint64_t* bytes) {
+  if (!m || !h_offsets || !bytes || (int)combine < HWAVE_SUM || (int)combine > HWAVE_MAX) return HWAVE_EINVAL;
+  std::vector<BulkJob> jobs;
+  std::vector<uint32_t> first;
+  GroupArgs a;
+  if (!group_plan(m, h_offsets, (int)combine, &jobs, &first, &a, bytes)) *bytes = 0;
+  return HWAVE_OK;
+}
+
+int hwave_multi_upsert_scratch(hwave_multi* m, const uint64_t* h_offsets, const void* d_keys, const void* d_vals,
+                               hwave_combine combine, uint8_t* d_status, void* d_scratch, uint64_t scratch_bytes,
+                               void* stream) {
+  if (!m || !h_offsets || (int)combine < HWAVE_SUM || (int)combine > HWAVE_MAX) return HWAVE_EINVAL;
+  std::vector<BulkJob> jobs;
+  std::vector<uint32_t> first;
+  GroupArgs a;
+  uint64_t bytes = 0;
+  if (!d_scratch || (uintptr_t)d_scratch % ALIGN || bad_ptr(d_keys) || bad_ptr(d_vals) ||
+      !group_plan(m, h_offsets, (int)combine, &jobs, &first, &a, &bytes) || bytes > scratch_bytes)
+    return hwave_multi_upsert(m, h_offsets, d_keys, d_vals, combine, d_status, stream);
+  // The jobs go to the scratch buffer through the staging buffer, which may still be
+  // in flight from the previous call.
+  const size_t n = jobs.size(), at = round_up(n * sizeof(BulkJob), ALIGN), list = at + first.size() * 4;
+  const int rc = multi_reserve(m, list / sizeof(MultiItem) + 1);
+  if (rc) return rc;
+  if (m->staged_pending) {
+    hipError_t e = hipEventSynchronize(m->staged);
+    if (e != hipSuccess) return hip_fail(e);
+  }
+  memcpy(m->h_stage, jobs.data(), n * sizeof(BulkJob));
+  memcpy((uint8_t*)m->h_stage + at, first.data(), first.size() * 4);
+  hipStream_t s = (hipStream_t)stream;
+  hipError_t e = hipMemcpyAsync(d_scratch, m->h_stage, list, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipEventRecord(m->staged, s);
+  if (e != hipSuccess) return hip_fail(e);
+  m->staged_pending = true;
+  a.g = BulkGroup{(const BulkJob*)d_scratch, (const uint32_t*)((uint8_t*)d_scratch + at), (uint32_t)n, (uint8_t*)d_scratch};
+  a.tables = m->d_tables;
+  e = m->shapes[0].ks->group_upsert(a, jobs.data(), d_keys, d_vals, (int)combine, d_status, s);
+  return e == hipSuccess ? HWAVE_OK : hip_fail(e);
 }
 
 }  // extern "C"

@@ -96,19 +96,19 @@ struct alignas(2 * sizeof(K)) BulkPair {
 // each pair to its place; the runs of one bin are short (a tile's share), and the
 // XCD's L2 merges them into lines.
 template <typename K, bool VALS, bool REC, int PER>
-__global__ void __launch_bounds__(BULK_SPLIT_THREADS)
-k_bulk_split(const K* __restrict__ keys, const K* __restrict__ vals, uint32_t n, uint32_t region_cap,
+__device__ __forceinline__ void
+bulk_split(uint32_t block, const K* __restrict__ keys, const K* __restrict__ vals, uint32_t n, uint32_t region_cap,
              const uint32_t* __restrict__ region_count, HomeMap home, uint32_t shift, uint32_t bins_log2, uint32_t bins,
              uint32_t cap, uint32_t* __restrict__ cursor, uint32_t cstride, K* __restrict__ rec,
              uint32_t* __restrict__ pos) {
   constexpr uint32_t TILE = BULK_SPLIT_THREADS * PER;
   __shared__ uint32_t hist[BULK_BINS], base[BULK_BINS];
   const uint32_t tid = threadIdx.x;
-  uint32_t region = 0, t0 = blockIdx.x * TILE, count = n;
+  uint32_t region = 0, t0 = block * TILE, count = n;
   if constexpr (REC) {
     const uint32_t tiles = (region_cap + TILE - 1) / TILE;
-    region = blockIdx.x / tiles;
-    t0 = (blockIdx.x % tiles) * TILE;
+    region = block / tiles;
+    t0 = (block % tiles) * TILE;
     count = region_count[region * BULK_CSTRIDE];
     if (count > region_cap) count = region_cap;
     if (t0 >= count) return;
@@ -160,6 +160,16 @@ k_bulk_split(const K* __restrict__ keys, const K* __restrict__ vals, uint32_t n,
     }
     pos[in0 + i] = dst;
   }
+}
+
+template <typename K, bool VALS, bool REC, int PER>
+__global__ void __launch_bounds__(BULK_SPLIT_THREADS)
+k_bulk_split(const K* __restrict__ keys, const K* __restrict__ vals, uint32_t n, uint32_t region_cap,
+             const uint32_t* __restrict__ region_count, HomeMap home, uint32_t shift, uint32_t bins_log2, uint32_t bins,
+             uint32_t cap, uint32_t* __restrict__ cursor, uint32_t cstride, K* __restrict__ rec,
+             uint32_t* __restrict__ pos) {
+  bulk_split<K, VALS, REC, PER>(blockIdx.x, keys, vals, n, region_cap, region_count, home, shift, bins_log2, bins, cap,
+                                cursor, cstride, rec, pos);
 }
 
 // Clears the cursors; mark: the erase flag of a table whose erases mark it before
@@ -772,39 +782,181 @@ k_bulk_back(uint32_t bins, uint32_t cap, const uint32_t* __restrict__ count, con
 
 // Statuses back to the call's order, and the operations left over (no room in their bin,
 // or BULK_PENDING) through the per-tile path, in that order.
+//
+// bulk_finish: 64 operations from `base` on, by one wave; pos null: none is decided.
+template <class C, bool ERASE>
+__device__ __forceinline__ void bulk_finish(const TableDev& tv, const typename C::K* __restrict__ keys,
+                                            const typename C::K* __restrict__ vals, uint64_t base, uint64_t n,
+                                            const uint32_t* __restrict__ pos, const uint8_t* __restrict__ stat,
+                                            int combine, uint8_t* __restrict__ out) {
+  __shared__ uint8_t order_lds[BLOCK];
+  using K = typename C::K;
+  const Tile<C::T> tile;
+  const uint32_t lane = __lane_id();
+  uint8_t* order = order_lds + __builtin_amdgcn_readfirstlane(threadIdx.x / 64) * 64;
+  bool rest = false;
+  if (base + lane < n) {
+    const uint32_t p = pos ? pos[base + lane] : BULK_NONE;
+    const uint8_t s = p == BULK_NONE ? BULK_PENDING : stat[p];
+    rest = s == BULK_PENDING;
+    if (!rest && out) out[base + lane] = s;
+  }
+  const uint64_t m = __ballot(rest);
+  if (m == 0) return;
+  if (rest) order[__popcll(m & ((1ull << lane) - 1))] = (uint8_t)lane;
+  wave_sync();
+  const uint32_t cnt = (uint32_t)__popcll(m);
+  for (uint32_t u = lane / C::T; u < cnt; u += 64 / C::T) {
+    const uint64_t j = base + order[u];
+    const K key = keys[j];
+    uint8_t s;
+    if constexpr (ERASE) s = Ops<C>::erase(tv, tile, key);
+    else s = Ops<C>::upsert(tv, tile, key, vals[j], combine);
+    if (out && tile.leader()) out[j] = s;
+  }
+  wave_sync();
+}
+
 template <class C, bool ERASE>
 __global__ void __launch_bounds__(BLOCK)
 k_bulk_finish(TableDev tv, const typename C::K* __restrict__ keys, const typename C::K* __restrict__ vals, uint32_t n,
               const uint32_t* __restrict__ pos, const uint8_t* __restrict__ stat, int combine,
               uint8_t* __restrict__ out) {
-  __shared__ uint8_t order_lds[BLOCK];
-  using K = typename C::K;
-  const Tile<C::T> tile;
   const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-  uint8_t* order = order_lds + wid * 64;
+  for (uint64_t base = ((uint64_t)blockIdx.x * (BLOCK / 64) + wid) * 64; base < n; base += (uint64_t)gridDim.x * BLOCK)
+    bulk_finish<C, ERASE>(tv, keys, vals, base, n, pos, stat, combine, out);
+}
+
+// ---------------------------------------------------------------- groups of tables
+//
+// One upsert per table of a group of one configuration: the same steps, each one
+// launch over all tables.  A step's blocks are numbered through the tables
+// (BulkGroup::first); a block looks its table up in that list, a wave at 64 places a
+// time, which costs one round trip to the L2 for every 64 tables.
+
+// A table of a group.
+struct MultiTable {
+  TableDev tv;
+  uint32_t cls;          // index in the key width's configuration menu
+  uint32_t pad;
+  uint64_t fill_words;   // 16-byte words of slots + tags (all-ones when empty)
+  uint64_t zero_words;   // 16-byte words of locks + control (zero when empty)
+};
+
+// One table's part in the call.
+struct BulkJob {
+  BulkPlan plan;      // levels 0: its operations are not grouped
+  HomeMap home;
+  uint32_t table;     // of the group
+  uint32_t n;         // operations
+  uint64_t begin;     // first operation, in the shared arrays
+  uint64_t scratch;   // offset of the plan's memory in the scratch buffer
+};
+
+enum : int { GROUP_ZERO, GROUP_SPLIT, GROUP_SPLIT2, GROUP_WRITE, GROUP_BACK, GROUP_FINISH, GROUP_STEPS };
+constexpr uint32_t GROUP_ZERO_BYTES = 4096;  // cleared per block of 256
+constexpr int GROUP_PER = 8;                 // operations per thread of a split tile
+
+struct BulkGroup {
+  const BulkJob* jobs;
+  const uint32_t* first;  // [GROUP_STEPS][n]: each job's first block of a step
+  uint32_t n;             // jobs
+  uint8_t* scratch;
+};
+
+// The job of this block, and the block's number within it (`rest`).
+template <int STEP>
+__device__ __forceinline__ const BulkJob& group_job(const BulkGroup& g, uint32_t* rest) {
+  const uint32_t* f = g.first + STEP * g.n;
   const uint32_t lane = __lane_id();
-  for (uint64_t base = ((uint64_t)blockIdx.x * (BLOCK / 64) + wid) * 64; base < n; base += (uint64_t)gridDim.x * BLOCK) {
-    bool rest = false;
-    if (base + lane < n) {
-      const uint32_t p = pos[base + lane];
-      const uint8_t s = p == BULK_NONE ? BULK_PENDING : stat[p];
-      rest = s == BULK_PENDING;
-      if (!rest && out) out[base + lane] = s;
-    }
-    const uint64_t m = __ballot(rest);
-    if (m == 0) continue;
-    if (rest) order[__popcll(m & ((1ull << lane) - 1))] = (uint8_t)lane;
-    wave_sync();
-    const uint32_t cnt = (uint32_t)__popcll(m);
-    for (uint32_t u = lane / C::T; u < cnt; u += 64 / C::T) {
-      const uint64_t j = base + order[u];
-      const K key = keys[j];
-      uint8_t s;
-      if constexpr (ERASE) s = Ops<C>::erase(tv, tile, key);
-      else s = Ops<C>::upsert(tv, tile, key, vals[j], combine);
-      if (out && tile.leader()) out[j] = s;
-    }
-    wave_sync();
+  uint32_t j = 0;  // jobs that start at or before this block
+  for (uint32_t i = 0; i < g.n; i += 64)
+    j += (uint32_t)__popcll(__ballot(i + lane < g.n && f[i + lane] <= blockIdx.x));
+  j = __builtin_amdgcn_readfirstlane(j) - 1;
+  *rest = blockIdx.x - __builtin_amdgcn_readfirstlane(f[j]);
+  return g.jobs[j];
+}
+
+template <typename K>
+__global__ void __launch_bounds__(256) k_group_clear(BulkGroup g) {
+  uint32_t b;
+  const BulkJob& j = group_job<GROUP_ZERO>(g, &b);
+  const uint64_t at = (uint64_t)b * GROUP_ZERO_BYTES + threadIdx.x * 16;
+  if (at < j.plan.zero_bytes) *(uint4*)(g.scratch + j.scratch + j.plan.off_cursor1 + at) = make_uint4(0, 0, 0, 0);
+}
+
+template <typename K, bool REC, int PER>
+__global__ void __launch_bounds__(BULK_SPLIT_THREADS)
+k_group_split(BulkGroup g, const K* __restrict__ keys, const K* __restrict__ vals) {
+  uint32_t b;
+  const BulkJob& j = group_job<REC ? GROUP_SPLIT2 : GROUP_SPLIT>(g, &b);
+  const BulkPlan& p = j.plan;
+  uint8_t* m = g.scratch + j.scratch;
+  uint32_t* cursor1 = (uint32_t*)(m + p.off_cursor1);
+  if constexpr (REC)
+    bulk_split<K, true, true, PER>(b, (const K*)(m + p.off_rec1), nullptr, p.bins * p.cap1, p.cap1, cursor1, j.home,
+                                   p.shift, p.sub, 1u << p.sub, p.cap, (uint32_t*)(m + p.off_cursor), 1,
+                                   (K*)(m + p.off_rec), (uint32_t*)(m + p.off_pos));
+  else
+    bulk_split<K, true, false, PER>(b, keys + j.begin, vals + j.begin, j.n, j.n, nullptr, j.home,
+                                    p.shift + (p.levels == 2 ? p.sub : 0), 0, p.bins, p.cap1, cursor1, BULK_CSTRIDE,
+                                    (K*)(m + p.off_rec1), (uint32_t*)(m + p.off_pos1));
+}
+
+template <class C>
+__global__ void __launch_bounds__(BULK_THREADS)
+k_group_write(BulkGroup g, const MultiTable* __restrict__ tables, int combine) {
+  using K = typename C::K;
+  extern __shared__ __align__(16) char bulk_lds[];
+  uint32_t part;
+  const BulkJob& j = group_job<GROUP_WRITE>(g, &part);
+  const BulkPlan& p = j.plan;
+  const TableDev tv = tables[j.table].tv;
+  uint8_t* m = g.scratch + j.scratch;
+  const bool two = p.levels == 2;
+  BulkLds<C, false> L;
+  L.place(bulk_lds, p.cap, p.hash_n, 1u << p.shift);
+  const uint32_t b0 = part << p.shift, left = Ops<C>::home_buckets(tv) - b0;
+  bulk_part<C, false>(tv, L, (const K*)(m + (two ? p.off_rec : p.off_rec1)) + (uint64_t)part * p.cap * 2,
+                      (const uint32_t*)(m + (two ? p.off_cursor : p.off_cursor1)) + (uint64_t)part * (two ? 1 : BULK_CSTRIDE),
+                      p.cap, p.hash_n, b0, left < (1u << p.shift) ? left : 1u << p.shift,
+                      p.slow_tiles < BULK_THREADS / C::T ? p.slow_tiles : BULK_THREADS / C::T, combine,
+                      m + (two ? p.off_stat : p.off_stat1) + (uint64_t)part * p.cap);
+}
+
+// (a block per 256 places of a first-level bin)
+template <typename K>
+__global__ void __launch_bounds__(256) k_group_back(BulkGroup g) {
+  uint32_t b;
+  const BulkJob& j = group_job<GROUP_BACK>(g, &b);
+  const BulkPlan& p = j.plan;
+  uint8_t* m = g.scratch + j.scratch;
+  const uint32_t per_bin = (p.cap1 + 255) / 256, bin = b / per_bin, off = b % per_bin * 256 + threadIdx.x;
+  const uint32_t have = ((const uint32_t*)(m + p.off_cursor1))[bin * BULK_CSTRIDE];
+  if (off >= (have < p.cap1 ? have : p.cap1)) return;
+  const uint64_t i = (uint64_t)bin * p.cap1 + off;
+  const uint32_t at = ((const uint32_t*)(m + p.off_pos))[i];
+  (m + p.off_stat1)[i] = at == BULK_NONE ? BULK_PENDING : (m + p.off_stat)[at];
+}
+
+// (a block per GROUP_FINISH_OPS operations)
+constexpr uint32_t GROUP_FINISH_OPS = 4 * BLOCK;
+template <class C>
+__global__ void __launch_bounds__(BLOCK)
+k_group_finish(BulkGroup g, const MultiTable* __restrict__ tables, const typename C::K* __restrict__ keys,
+               const typename C::K* __restrict__ vals, int combine, uint8_t* __restrict__ out) {
+  uint32_t b;
+  const BulkJob& j = group_job<GROUP_FINISH>(g, &b);
+  const TableDev tv = tables[j.table].tv;
+  const uint8_t* m = g.scratch + j.scratch;
+  const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const bool grouped = j.plan.levels != 0;
+  for (uint32_t k = 0; k < GROUP_FINISH_OPS / BLOCK; ++k) {
+    const uint64_t base = (uint64_t)b * GROUP_FINISH_OPS + k * BLOCK + wid * 64;
+    if (base < j.n)
+      bulk_finish<C, false>(tv, keys + j.begin, vals + j.begin, base, j.n,
+                            grouped ? (const uint32_t*)(m + j.plan.off_pos1) : nullptr, m + j.plan.off_stat1, combine,
+                            out ? out + j.begin : nullptr);
   }
 }
 

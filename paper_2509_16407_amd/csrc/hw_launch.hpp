@@ -262,6 +262,16 @@ typedef hipError_t (*mixed_fn)(const LaunchArgs&, const uint8_t*, const void*, c
 typedef hipError_t (*bulk_fn)(const LaunchArgs&, const BulkPlan&, uint8_t*, const void*, const void*, uint32_t, int,
                               uint8_t*, hipStream_t);
 
+// One upsert per table of a group (hw_bulk.hpp): blocks[] per step, `lds` bytes for k_group_write.
+struct GroupArgs {
+  BulkGroup g;
+  const MultiTable* tables;
+  uint32_t blocks[GROUP_STEPS];
+  uint64_t n;  // operations of all tables
+};
+typedef hipError_t (*group_fn)(const GroupArgs&, const BulkJob* host_jobs, const void*, const void*, int, uint8_t*,
+                               hipStream_t);
+
 struct KernelSet {
   int kv_bits, design, bucket, tile;
   bool bsp;  // phased variant (no locks, plain loads in queries)
@@ -271,6 +281,7 @@ struct KernelSet {
   mixed_fn mixed;
   int bulk_slots;  // most slots per part of a grouped call
   bulk_fn bulk_upsert, bulk_erase;  // grouped by bucket (hw_bulk.hpp); null: the design has no such form
+  group_fn group_upsert;            // the same over a group of tables
 };
 
 template <class C>
@@ -339,6 +350,26 @@ struct Launch {
     }
     hipLaunchKernelGGL((k_bulk_finish<C, ERASE>), dim3(grid), dim3(BLOCK), 0, s, a.tv, (const K*)keys,
                        ERASE ? (const K*)keys : v, n, pos1, stat1, combine, status);
+    return hipGetLastError();
+  }
+  static hipError_t group(const GroupArgs& a, const BulkJob* jobs, const void* keys, const void* vals, int combine,
+                          uint8_t* status, hipStream_t s) {
+    uint32_t lds = 0;
+    for (uint32_t i = 0; i < a.g.n; ++i) {
+      const BulkPlan& p = jobs[i].plan;
+      BulkLds<C, false> L;
+      if (p.levels) lds = std::max(lds, L.place(nullptr, p.cap, p.hash_n, 1u << p.shift));
+    }
+    const K *k = (const K*)keys, *v = (const K*)vals;
+    auto on = [&](int step) { return dim3(a.blocks[step]); };
+    hipLaunchKernelGGL((k_group_clear<K>), on(GROUP_ZERO), dim3(256), 0, s, a.g);
+    hipLaunchKernelGGL((k_group_split<K, false, GROUP_PER>), on(GROUP_SPLIT), dim3(BULK_SPLIT_THREADS), 0, s, a.g, k, v);
+    if (a.blocks[GROUP_SPLIT2])
+      hipLaunchKernelGGL((k_group_split<K, true, GROUP_PER>), on(GROUP_SPLIT2), dim3(BULK_SPLIT_THREADS), 0, s, a.g, k, v);
+    hipLaunchKernelGGL((k_group_write<C>), on(GROUP_WRITE), dim3(BULK_THREADS), lds, s, a.g, a.tables, combine);
+    if (a.blocks[GROUP_BACK]) hipLaunchKernelGGL((k_group_back<K>), on(GROUP_BACK), dim3(256), 0, s, a.g);
+    hipLaunchKernelGGL((k_group_finish<C>), on(GROUP_FINISH), dim3(BLOCK), 0, s, a.g, a.tables, k, v, combine,
+                       status);
     return hipGetLastError();
   }
   // One level of the split; REC: from the regions of the level before.
@@ -413,9 +444,16 @@ constexpr bulk_fn bulk_of() {
 }
 
 template <class C>
+constexpr group_fn group_of() {
+  if constexpr (bulk_of<C, false>() != nullptr) return &Launch<C>::group;
+  else return nullptr;
+}
+
+template <class C>
 constexpr KernelSet make_set() {
   return KernelSet{(int)sizeof(typename C::K) * 8, C::DESIGN, C::B, C::T, C::BSP, &Launch<C>::upsert,
-                   &Launch<C>::query, &Launch<C>::erase, &Launch<C>::mixed, bulk_slots<C>(), bulk_of<C, false>(), bulk_of<C, true>()};
+                   &Launch<C>::query, &Launch<C>::erase, &Launch<C>::mixed, bulk_slots<C>(), bulk_of<C, false>(), bulk_of<C, true>(),
+                   group_of<C>()};
 }
 
 // Instance tables, one per translation unit.

@@ -40,14 +40,6 @@ struct MultiItem {
   uint64_t end;
 };
 
-struct MultiTable {
-  TableDev tv;
-  uint32_t cls;          // index in the key width's configuration menu
-  uint32_t pad;
-  uint64_t fill_words;   // 16-byte words of slots + tags (all-ones when empty)
-  uint64_t zero_words;   // 16-byte words of locks + control (zero when empty)
-};
-
 struct MultiQueues {
   uint32_t start[NQ];  // item index where queue q starts
   uint32_t end[NQ];
