@@ -975,6 +975,12 @@ namespace {
 // work to give every wave of the persistent grid several chunks.
 constexpr uint64_t MULTI_CHUNK = 16384;
 constexpr uint64_t MULTI_CHUNK_MIN = 256;
+// A wave works through a chunk one tile-full after the other, so calls of few operations
+// get smaller ones (16 tables of 2^20 slots, 8000 queries each: 151 us with 256, 82 with
+// 64; 60,000 each 179 with 256, 197 with 117).  Writes only while the chunks put no more tiles
+// to work than the table has home buckets: more of them queue longer for its locks
+// (40 tables of 2^12 slots, 1.7 operations per slot: 630 us with 256, 761 with 64).
+constexpr uint64_t MULTI_CHUNK_LEAST = 64;
 // Tables whose footprint fits comfortably in one XCD's L2 keep all their items on
 // one queue.
 constexpr uint64_t L2_RESIDENT_BYTES = 2ull << 20;
@@ -1126,6 +1132,7 @@ int hwave_multi_run(hwave_multi* m, const hwave_item* h_items, uint32_t n_items,
   const uint64_t waves = (uint64_t)m->grid * (BLOCK / 64);
   uint64_t chunk = total_ops / (4 * waves);
   if (chunk > MULTI_CHUNK) chunk = MULTI_CHUNK;
+  const uint64_t least = std::max(chunk, std::min(MULTI_CHUNK_MIN, std::max(MULTI_CHUNK_LEAST, 4 * total_ops / waves)));
   if (chunk < MULTI_CHUNK_MIN) chunk = MULTI_CHUNK_MIN;
   for (uint32_t i = 0; i < n_items; i++) {
     const hwave_item& it = h_items[i];
@@ -1136,12 +1143,15 @@ int hwave_multi_run(hwave_multi* m, const hwave_item* h_items, uint32_t n_items,
     const int comb = (int)((it.op >> 8) & 0xFF);
     if (op == HWAVE_OP_UPSERT && (comb == HWAVE_SUM || comb == HWAVE_MIN || comb == HWAVE_MAX)) merging = true;
     const bool small = m->table_bytes[it.table] <= L2_RESIDENT_BYTES;
-    for (uint64_t b = it.begin; b < it.end; b += chunk) {
+    uint64_t step = least;
+    if (op != HWAVE_OP_QUERY)
+      step = std::min(std::max(least, 16 * (it.end - it.begin) / std::max<uint64_t>(1, m->shapes[it.table].nbh)), std::max(least, chunk));
+    for (uint64_t b = it.begin; b < it.end; b += step) {
       MultiItem c;
       c.table = it.table;
       c.op = it.op;
       c.begin = b;
-      c.end = b + chunk < it.end ? b + chunk : it.end;
+      c.end = b + step < it.end ? b + step : it.end;
       const uint32_t q = small ? it.table % NQ : (rr++ % NQ);
       per_q[q].push_back(c);
     }
@@ -1170,7 +1180,11 @@ int hwave_multi_run(hwave_multi* m, const hwave_item* h_items, uint32_t n_items,
   if (e == hipSuccess) e = hipEventRecord(m->staged, s);
   if (e != hipSuccess) return hip_fail(e);
   m->staged_pending = true;
-  e = launch_multi(m->kv_bits, m->menu, m->solo, m->agg, m->grid, m->d_tables, m->d_items, qs, m->d_heads, d_keys,
+  // Two waves per item where that is fewer than the chip holds: every wave looks at every
+  // queue's head before it ends, and one address serves ~80 M atomics a second (2560
+  // queries on 10 tables: 143 us with the whole grid, 29 so).
+  const unsigned grid = (unsigned)std::min<uint64_t>(m->grid, (2 * total + BLOCK / 64 - 1) / (BLOCK / 64));
+  e = launch_multi(m->kv_bits, m->menu, m->solo, m->agg, grid, m->d_tables, m->d_items, qs, m->d_heads, d_keys,
                    d_vals ? d_vals : d_keys, d_vals_out, d_status, s);
   if (e == hipSuccess && merging) e = launch_multi_hot_flush(m->kv_bits, m->d_tables, m->d_hot, m->n_hot, s);
   return e == hipSuccess ? HWAVE_OK : hip_fail(e);

@@ -124,17 +124,24 @@ k_multi(const MultiTable* __restrict__ tables, const MultiItem* __restrict__ ite
         uint32_t* heads, const void* keys, const void* vals, void* out, uint8_t* status) {
   __shared__ AggLds<typename M::K> agg_lds[M::AGGREGATE ? BLOCK / 64 : 1];
   AggLds<typename M::K>& agg = agg_lds[M::AGGREGATE ? threadIdx.x / 64 : 0];
+  __shared__ uint32_t drained;  // queues that a wave of this block found empty
+  if (threadIdx.x == 0) drained = 0;
+  __syncthreads();
   const uint32_t lane = __lane_id();
   const uint32_t home = blockIdx.x % NQ;
   for (uint32_t k = 0; k < NQ; ++k) {
     const uint32_t q = (home + k) % NQ;
     const uint32_t qlen = qs.end[q] - qs.start[q];
+    if (__hip_atomic_load(&drained, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> q & 1) continue;
     while (true) {
       uint32_t idx = 0;
       if (lane == 0)
         idx = __hip_atomic_fetch_add(heads + q * HEAD_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       idx = __builtin_amdgcn_readfirstlane(idx);
-      if (idx >= qlen) break;
+      if (idx >= qlen) {
+        if (lane == 0) __hip_atomic_fetch_or(&drained, 1u << q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        break;
+      }
       const MultiItem m = items[qs.start[q] + idx];
       const MultiTable& t = tables[m.table];
       dispatch(__builtin_amdgcn_readfirstlane(t.cls), t.tv, m, keys, vals, out, status, agg, M{});
