@@ -36,7 +36,8 @@ namespace hw {
 constexpr uint32_t MERGE_CHUNK = 1u << 20;        // operations per pass (library workspace)
 constexpr uint32_t MERGE_NONE = 0xFFFFFFFFu;      // op_ent of an operation that is not merged
 constexpr uint32_t MERGE_FOLLOWER = 0x80000000u;  // op_ent flag set by a follower in pass 2
-constexpr int MERGE_BLOCK_OPS = 4096;             // operations per block window of pass 1
+constexpr int MERGE_BLOCK_OPS = 4096;             // operations per block window of pass 1 ...
+constexpr int MERGE_SMALL_OPS = 1024;             // ... and of calls that would leave most of the chip idle
 constexpr int MERGE_THREADS = 1024;               // threads per block of pass 1 (16 waves: latency hiding)
 constexpr int MERGE_LDS = 2048;                   // LDS entries per block (upserts <= 30% of 4096 in
                                                   // mixed batches; more spill to the global table)
@@ -101,7 +102,7 @@ __device__ __forceinline__ uint32_t merge_slot(const MergeWs& ws, uint64_t k) {
 
 // Pass 1 over ops [0, n) (n <= ws.chunk): upserts (ops[i] == OP_UPSERT, valid key)
 // are merged; op_ent receives each operation's entry or MERGE_NONE.
-template <typename K>
+template <typename K, int PER>
 __global__ void __launch_bounds__(MERGE_THREADS)
 k_merge_build(MergeWs ws, const uint8_t* __restrict__ ops, const K* __restrict__ keys,
               const K* __restrict__ vals, uint64_t n, int combine) {
@@ -109,9 +110,9 @@ k_merge_build(MergeWs ws, const uint8_t* __restrict__ ops, const K* __restrict__
   __shared__ uint64_t lacc[MERGE_LDS];
   __shared__ uint32_t llead[MERGE_LDS];
   __shared__ uint32_t lgent[MERGE_LDS];
-  constexpr int PER = MERGE_BLOCK_OPS / MERGE_THREADS;
+  constexpr int WINDOW = PER * MERGE_THREADS;
   const uint32_t tid = threadIdx.x;
-  for (uint64_t c0 = (uint64_t)blockIdx.x * MERGE_BLOCK_OPS; c0 < n; c0 += (uint64_t)gridDim.x * MERGE_BLOCK_OPS) {
+  for (uint64_t c0 = (uint64_t)blockIdx.x * WINDOW; c0 < n; c0 += (uint64_t)gridDim.x * WINDOW) {
     for (uint32_t e = tid; e < MERGE_LDS; e += MERGE_THREADS) {
       lkey[e] = ~0ull;
       lacc[e] = 0;

@@ -980,11 +980,13 @@ struct Ops {
           __builtin_amdgcn_s_sleep(2);
         }
       } else {
-        // a retry (LOOK: at first, a try): a pause of 2^retries steps of 64 cycles, at most
-        // 2^LOCK_SPINS, then a look at the byte and the OR if it reads clear
+        // retry number `retries` (LOOK: at first 0, a try): a pause that doubles from 128
+        // cycles up to that of retry LOCK_SPINS, then a look at the byte and the OR if
+        // it reads clear
         const uint32_t retries = ws[3];
         if (!LOOK || retries)
-          for (uint32_t i = 0; i < (1u << (retries < LOCK_SPINS ? retries : LOCK_SPINS)); ++i) __builtin_amdgcn_s_sleep(1);
+          for (uint32_t i = 0; i < (1u << ((LOOK && retries > LOCK_SPINS ? LOCK_SPINS : retries) - 1)); ++i)
+            __builtin_amdgcn_s_sleep(2);
         if (LOOK && look_up()) {
           status = ST_EXISTED;
           stage = DONE;
