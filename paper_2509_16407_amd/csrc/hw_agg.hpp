@@ -48,8 +48,8 @@ __device__ __forceinline__ K agg_identity(int combine) {
 // Applies ops [i0, i0 + n) of `keys`/`vals` (n <= AGG_WIN, the same combine for
 // all) to the table through the merge table L.  Writes status[i] if non-null.
 // `row` < HOT_ROWS picks the hot-key accumulator row.  Called by all 64 lanes of
-// the wave together.
-template <class C>
+// the wave together.  LOOK: see Ops::upsert.
+template <class C, bool LOOK>
 __device__ void agg_window(const TableDev& tv, AggLds<typename C::K>& L, const typename C::K* __restrict__ keys,
                            const typename C::K* __restrict__ vals, uint64_t i0, uint32_t n, int combine,
                            uint8_t* __restrict__ status, uint32_t row) {
@@ -113,7 +113,7 @@ __device__ void agg_window(const TableDev& tv, AggLds<typename C::K>& L, const t
   const uint32_t first = (uint32_t)(((uint64_t)(uint32_t)(i0 / AGG_WIN * 0x9E3779B1u) * n_u) >> 32);
   for (uint32_t u = lane / C::T; u < n_u; u += 64 / C::T) {
     const uint32_t e = L.list[u + first < n_u ? u + first : u + first - n_u];
-    const uint8_t st = Ops<C>::template upsert<true>(tv, tile, L.key[e], L.val[e], combine, L.stat[e] ? (int)row : -1);
+    const uint8_t st = Ops<C>::template upsert<LOOK>(tv, tile, L.key[e], L.val[e], combine, L.stat[e] ? (int)row : -1);
     if (tile.leader()) L.stat[e] = st;
   }
   wave_sync();

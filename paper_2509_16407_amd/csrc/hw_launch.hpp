@@ -41,7 +41,7 @@ k_upsert_agg(TableDev tv, const typename C::K* __restrict__ keys, const typename
   const uint64_t n_waves = (uint64_t)gridDim.x * (BLOCK / 64);
   for (uint64_t i0 = wave * AGG_WIN; i0 < n; i0 += n_waves * AGG_WIN) {
     const uint64_t left = n - i0;
-    agg_window<C>(tv, L, keys, vals, i0, (uint32_t)(left < AGG_WIN ? left : AGG_WIN), combine, status,
+    agg_window<C, true>(tv, L, keys, vals, i0, (uint32_t)(left < AGG_WIN ? left : AGG_WIN), combine, status,
                   (uint32_t)(wave % HOT_ROWS));
   }
 }

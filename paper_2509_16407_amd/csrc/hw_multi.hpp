@@ -50,6 +50,9 @@ struct Menu {
   static constexpr int N = 1 + sizeof...(Cs);
   static constexpr bool AGGREGATE = AGG;  // compiled with the merging path (hw_agg.hpp)
   using K = typename C0::K;               // one key width per menu
+  // a second look for absent keys (Ops::upsert) costs a menu's kernel more than it gives: its plain writes
+  // spill more (4 tables of 2^16 slots, 30,000 skewed upserts each: 5.9 ms, 6.6 with it)
+  static constexpr bool LOOK = false;
   // occupancy target: cuckoo's three-lock paths need more registers
   static constexpr int WAVES = (C0::CUCKOO || ... || Cs::CUCKOO) ? 4 : HW_MULTI_WAVES;
 };
@@ -60,6 +63,7 @@ struct Menu {
 // and spills, and with them two of its eight waves per SIMD.
 template <class M, int W>
 struct Solo : M {
+  static constexpr bool LOOK = true;  // 10^6 Zipf operations on a fresh table: 1.60 ms without, 0.43 with it
   static constexpr int WAVES = W;
 };
 
@@ -71,7 +75,7 @@ constexpr int solo_waves(bool agg) {
 }
 
 // Runs ops [m.begin, m.end) of one table with configuration C on this wave.
-template <class C, bool AGG>
+template <class C, bool AGG, bool LOOK>
 __device__ __forceinline__ void run_item(const TableDev& tv, const MultiItem& m, const typename C::K* __restrict__ keys,
                          const typename C::K* __restrict__ vals, typename C::K* __restrict__ out,
                          uint8_t* __restrict__ status, AggLds<typename C::K>& agg) {
@@ -84,7 +88,7 @@ __device__ __forceinline__ void run_item(const TableDev& tv, const MultiItem& m,
     if ((op == OP_INSERT || op == OP_UPSERT) && tv.aggregate && agg_merges(combine)) {
       for (uint64_t i0 = m.begin; i0 < m.end; i0 += AGG_WIN) {
         const uint64_t left = m.end - i0;
-        agg_window<C>(tv, agg, keys, vals, i0, (uint32_t)(left < AGG_WIN ? left : AGG_WIN), combine, status,
+        agg_window<C, LOOK>(tv, agg, keys, vals, i0, (uint32_t)(left < AGG_WIN ? left : AGG_WIN), combine, status,
                       (blockIdx.x * (BLOCK / 64) + threadIdx.x / 64) % HOT_ROWS);
       }
       return;
@@ -106,12 +110,12 @@ __device__ __forceinline__ void run_item(const TableDev& tv, const MultiItem& m,
   }
 }
 
-template <bool AGG, class... Cs>
+template <bool LOOK, bool AGG, class... Cs>
 __device__ __forceinline__ void dispatch(uint32_t cls, const TableDev& tv, const MultiItem& m,
                                          const void* keys, const void* vals, void* out, uint8_t* status,
                                          AggLds<typename Menu<AGG, Cs...>::K>& agg, Menu<AGG, Cs...>) {
   uint32_t i = 0;
-  (void)((cls == i++ ? (run_item<Cs, AGG>(tv, m, (const typename Cs::K*)keys, (const typename Cs::K*)vals,
+  (void)((cls == i++ ? (run_item<Cs, AGG, LOOK>(tv, m, (const typename Cs::K*)keys, (const typename Cs::K*)vals,
                                      (typename Cs::K*)out, status, agg),
                         true)
                      : false) ||
@@ -144,7 +148,7 @@ k_multi(const MultiTable* __restrict__ tables, const MultiItem* __restrict__ ite
       }
       const MultiItem m = items[qs.start[q] + idx];
       const MultiTable& t = tables[m.table];
-      dispatch(__builtin_amdgcn_readfirstlane(t.cls), t.tv, m, keys, vals, out, status, agg, M{});
+      dispatch<M::LOOK>(__builtin_amdgcn_readfirstlane(t.cls), t.tv, m, keys, vals, out, status, agg, M{});
     }
   }
 }

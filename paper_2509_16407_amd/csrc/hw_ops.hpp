@@ -911,16 +911,27 @@ struct Ops {
     else __hip_atomic_fetch_min(vp, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 
+  // The tile's waiting state (ticket, start of the wait, next look, retries or
+  // looks): in LDS, one slot per tile of the block, because it is touched only
+  // while waiting, and kept out of registers it leaves them to the critical
+  // section.  Every lane of a tile writes the same values.
+  __device__ static __forceinline__ uint32_t* wait_state() {
+    __shared__ uint32_t wait_lds[4 * (BLOCK / T)];
+    return wait_lds + 4 * (threadIdx.x / T);
+  }
+
   // Runs cs() under bucket b's lock (hw_device.hpp) and returns its status, or
-  // ST_EXISTED when look_up() did without the lock (LOOK), or ST_TIMEOUT when the wait outlasted the table's limit or another waiter of
+  // ST_TIMEOUT when the wait outlasted the table's limit or another waiter of
   // the table reported such a failure (checked on every 16th look).
   //
-  // The tile tries the lock byte; if it is held, it retries up to `spins`
+  // The tile tries the lock byte; if it is held, it retries up to LOCK_SPINS
   // times, each after a growing pause and only when the byte reads clear (a
   // lock held by one other tile is usually free again within a critical
-  // section).  LOOK: before each try look_up() may settle the operation.  Then it takes a ticket of the bucket's lock queue, looks at the
+  // section).  Then it takes a ticket of the bucket's lock queue, looks at the
   // serving counter at times spaced by its place in the queue, and once at the
-  // head tries the byte until it takes it, then passes the queue on.
+  // head tries the byte until it takes it, then passes the queue on.  LOOK: after
+  // LOCK_SPINS retries look_up() may settle the operation without the lock
+  // (ST_EXISTED), and again after as many more, before the ticket.
   //
   // Lanes of a wave run in lockstep, so every tile of the wave goes round this
   // loop until the last one is done.  The critical section comes first in each
@@ -929,18 +940,11 @@ struct Ops {
   // round trips (the retries, the most common wait, come last in the round),
   // and tiles of one wave that wait on each other cannot deadlock.
   template <bool LOOK, class G, class F>
-  __device__ static uint8_t locked(const TableDev& tv, const Tile<T>& tile, uint32_t b, uint32_t spins, G&& look_up,
-                                   F&& cs) {
-    // The waiting state (ticket, start of the wait, next look, retries or
-    // looks) lives in LDS, one slot per tile of the block: it is touched only
-    // while waiting, and kept out of registers it leaves them to the critical
-    // section inlined below.  Every lane of a tile writes the same values.
-    __shared__ uint32_t wait_lds[4 * (BLOCK / T)];
-    uint32_t* const ws = wait_lds + 4 * (threadIdx.x / T);
+  __device__ static uint8_t locked(const TableDev& tv, const Tile<T>& tile, uint32_t b, G&& look_up, F&& cs) {
+    uint32_t* const ws = wait_state();
     enum : uint32_t { HAVE = 0, RETRY = 1, QUEUED = 2, HEAD = 3, DONE = 4 };
-    uint32_t stage = RETRY;
-    if (!LOOK && try_lock(tv.locks, b, tile)) stage = HAVE;
-    if (stage == RETRY) ws[3] = LOOK ? 0 : 1;
+    uint32_t stage = try_lock(tv.locks, b, tile) ? HAVE : RETRY;
+    if (stage == RETRY) ws[3] = 0;
     uint8_t status = ST_TIMEOUT;
     while (stage != DONE) {
       if (stage == HAVE) {
@@ -980,19 +984,16 @@ struct Ops {
           __builtin_amdgcn_s_sleep(2);
         }
       } else {
-        // retry number `retries` (LOOK: at first 0, a try): a pause that doubles from 128
-        // cycles up to that of retry LOCK_SPINS, then a look at the byte and the OR if
-        // it reads clear
-        const uint32_t retries = ws[3];
-        if (!LOOK || retries)
-          for (uint32_t i = 0; i < (1u << ((LOOK && retries > LOCK_SPINS ? LOCK_SPINS : retries) - 1)); ++i)
-            __builtin_amdgcn_s_sleep(2);
-        if (LOOK && look_up()) {
+        // retry: a pause of 2^retries steps of 128 cycles (at most of 2^(LOCK_SPINS - 1)),
+        // then a look at the byte and the OR if it reads clear
+        const uint32_t retries = ws[3], pause = LOOK && retries >= LOCK_SPINS ? LOCK_SPINS - 1 : retries;
+        for (uint32_t i = 0; i < (1u << pause); ++i) __builtin_amdgcn_s_sleep(2);
+        if (lock_looks_free(tv.locks, b, tile) && try_lock(tv.locks, b, tile)) {
+          stage = HAVE;
+        } else if (LOOK && (retries + 1) % LOCK_SPINS == 0 && look_up()) {
           status = ST_EXISTED;
           stage = DONE;
-        } else if (((LOOK && retries == 0) || lock_looks_free(tv.locks, b, tile)) && try_lock(tv.locks, b, tile)) {
-          stage = HAVE;
-        } else if (retries == spins) {
+        } else if (retries + 1 == (LOOK ? 2 * LOCK_SPINS : LOCK_SPINS)) {
           const uint64_t w = take_ticket(tv.lockq, b & tv.lockq_mask, tile);
           const uint32_t mine = (uint32_t)(w >> 32), since = now_ticks();
           stage = (uint32_t)w == mine ? HEAD : QUEUED;
@@ -1025,11 +1026,13 @@ struct Ops {
   // SUM/MIN/MAX combine of a present key goes to row hot_row of the accumulators
   // instead of the value word.
   //
-  // LOOK (windows of merged operations): a tile that finds the lock held looks for
-  // its key again before each retry.  At the start of a skewed batch every window
-  // holds the same few absent keys; once the first of them has inserted a key, the
-  // others need no lock, where each used to wait in line for it (4 M operations on
-  // 1.6 M Zipf keys, the upsert alone: 4 to 7 ms before, 1.8 after).
+  // LOOK (windows of merged operations): a tile whose retries found the lock held
+  // looks for its key again before it joins the lock's queue.  At the start of a
+  // skewed batch every window holds the same few absent keys; once the first of
+  // them has inserted a key, the others need no lock, where each would wait in line
+  // for it (1.5 M Zipf operations on a fresh P2HT(M) of 2^21 slots: 7.7 ms without,
+  // 0.54 with it; as many distinct keys 0.450 and 0.456, 0.525 with a look before every
+  // retry).
   template <bool LOOK = false>
   __device__ static uint8_t upsert(const TableDev& tv, const Tile<T>& tile, K key, K val,
                                    int combine, int hot_row = -1) {
@@ -1061,11 +1064,9 @@ struct Ops {
     // two writers of one chain (only its queries differ, Table 1's phased column).
     if constexpr (C::BSP && !C::CHAIN) {
       if (erase) return erase_locked(tv, tile, h, key, tag);
-      return upsert_locked(tv, tile, h, key, val, tag, combine);
+      return upsert_locked<false>(tv, tile, h, key, val, tag, combine);
     }
-    const bool stable = !erase && tv.no_erase;
-    auto look_up = [&]() -> bool {
-      if (!stable) return false;
+    auto look_up = [&]() -> bool {  // a present key of a table that never erases
       K cur;
       const int64_t s = find(tv, tile, h, key, tag, &cur);
       if (s < 0) return false;
@@ -1076,22 +1077,22 @@ struct Ops {
       }
       return true;
     };
-    if (!LOOK && look_up()) return ST_EXISTED;
-    return locked<LOOK>(tv, tile, h.b1, LOOK && stable ? 2 * LOCK_SPINS : LOCK_SPINS, look_up, [&]() -> uint8_t {
+    if (!erase && tv.no_erase && look_up()) return ST_EXISTED;
+    return locked<LOOK>(tv, tile, h.b1, [&]() -> bool { return tv.no_erase && look_up(); }, [&]() -> uint8_t {
       if (erase) return erase_locked(tv, tile, h, key, tag);
-      return upsert_locked(tv, tile, h, key, val, tag, combine);
+      return upsert_locked<false>(tv, tile, h, key, val, tag, combine);
     });
   }
 
-  // Finds or inserts `key` under its home bucket's lock; `shared`: other tiles work
+  // Finds or inserts `key` under its home bucket's lock; SHARED: other tiles work
   // under the same lock, on other keys (not in chains).
+  template <bool SHARED>
   __device__ static __forceinline__ uint8_t upsert_locked(const TableDev& tv, const Tile<T>& tile, const Home& h,
-                                                          K key, K val, uint32_t tag, int combine,
-                                                          bool shared = false) {
+                                                          K key, K val, uint32_t tag, int combine) {
     if constexpr (C::CHAIN)
       return upsert_chain_locked(tv, tile, h, key, val, combine);
     else if constexpr (C::ICEBERG)
-      return upsert_iceberg_locked(tv, tile, h, key, val, tag, combine, !C::BSP && !shared);
+      return upsert_iceberg_locked<!C::BSP && !SHARED>(tv, tile, h, key, val, tag, combine);
     else if constexpr (C::DOUBLE)
       return upsert_double_locked(tv, tile, h, key, val, tag, combine);
     else
@@ -1192,9 +1193,10 @@ struct Ops {
   // Iceberg insert under the front bucket's lock: the front bucket if it has a
   // free slot (after checking the backyard for the key once an erase has
   // happened), else the less loaded backyard choice, ties to the first.
+  template <bool EXCL>
   __device__ static uint8_t upsert_iceberg_locked(const TableDev& tv, const Tile<T>& tile,
                                                   const Home& h, K key, K val, uint32_t tag,
-                                                  int combine, bool excl) {
+                                                  int combine) {
     if (tile.leader()) probe_add(tv, PC_WRITE, 1);
     BucketScan<K> rf = scan<true>(tv, tile, h.b1, key, tag);
     if (tile.leader()) probe_add(tv, PC_VISIT, 1);
@@ -1205,8 +1207,8 @@ struct Ops {
     // Front-yard slots are claimed only under this lock: plain stores suffice
     // (not in the phased variant, which takes no lock, nor where tiles share it).
     if (rf.free >= 0 && !erased(tv, tile)) {
-      if (claim_in_bucket(tv, tile, h.b1, rf, key, val, tag, excl) >= 0) return ST_DONE;
-      rf = scan<false>(tv, tile, h.b1, key, tag);  // (not excl) lost the slot to another key
+      if (claim_in_bucket(tv, tile, h.b1, rf, key, val, tag, EXCL) >= 0) return ST_DONE;
+      rf = scan<false>(tv, tile, h.b1, key, tag);  // (not EXCL) lost the slot to another key
     }
     BucketScan<K> r1 = scan<true>(tv, tile, h.h2, key, tag);
     if (tile.leader()) probe_add(tv, PC_VISIT, 1);
@@ -1223,7 +1225,7 @@ struct Ops {
         return ST_EXISTED;
       }
     }
-    if (rf.free >= 0 && claim_in_bucket(tv, tile, h.b1, rf, key, val, tag, excl) >= 0) return ST_DONE;
+    if (rf.free >= 0 && claim_in_bucket(tv, tile, h.b1, rf, key, val, tag, EXCL) >= 0) return ST_DONE;
     if (h.b3 == h.h2) return claim_in_bucket(tv, tile, h.h2, r1, key, val, tag) >= 0 ? ST_DONE : ST_FULL;
     return claim_less_loaded(tv, tile, h.h2, r1, h.b3, r2, key, val, tag);
   }

@@ -1,0 +1,63 @@
+"""What the compiler made of the kernels (CPU only): the persistent multi-table kernels
+have the registers and LDS for the occupancy that sizes their grids."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+import paper_2509_16407_amd as hw
+
+LLVM = "/opt/rocm/llvm/bin/"
+pytestmark = pytest.mark.skipif(not os.path.exists(LLVM + "llvm-readelf"), reason="no LLVM tools")
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def code_objects(so, tmp):
+    """The gfx950 code objects of the library, one per source with kernels."""
+    fat = os.path.join(tmp, "fat")
+    subprocess.check_call([LLVM + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + fat, so, os.path.join(tmp, "x.so")])
+    d = open(fat, "rb").read()
+    at = d.find(MAGIC)
+    while at >= 0:
+        n, = struct.unpack_from("<Q", d, at + 24)
+        p = at + 32
+        for _ in range(n):
+            off, size, tlen = struct.unpack_from("<QQQ", d, p)
+            triple = d[p + 24: p + 24 + tlen]
+            p += 24 + tlen
+            if b"gfx950" in triple and size:
+                path = os.path.join(tmp, "co%d" % at)
+                with open(path, "wb") as f:
+                    f.write(d[at + off: at + off + size])
+                yield path
+        at = d.find(MAGIC, at + 1)
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """name -> (VGPRs, LDS bytes) of every kernel."""
+    res = {}
+    for co in code_objects(hw.LIB_PATH, str(tmp_path_factory.mktemp("co"))):
+        text = subprocess.run([LLVM + "llvm-readelf", "--notes", co], capture_output=True, text=True,
+                              check=True).stdout
+        for doc in re.split(r"^  - \.ag", text, flags=re.M)[1:]:
+            f = dict(re.findall(r"\.(name|vgpr_count|group_segment_fixed_size): +(\S+)$", doc, re.M))
+            res[f["name"]] = (int(f["vgpr_count"]), int(f["group_segment_fixed_size"]))
+    names = subprocess.run(["c++filt"], input="\n".join(res), capture_output=True, text=True, check=True).stdout.split("\n")
+    return dict(zip(names, res.values()))
+
+
+def test_multi_table_kernels_meet_their_occupancy(kernels):
+    """Waves per SIMD: as many as registers (512 per lane, granules of 8) and LDS (160 KB,
+    blocks of one wave per SIMD) allow, at least the kernel's target."""
+    seen = 0
+    for name, (vgprs, lds) in kernels.items():
+        if "k_multi<" not in name:
+            continue
+        solo = re.search(r"k_multi<hw::Solo<.*, (\d+)> ?>\(", name)
+        waves = int(solo.group(1)) if solo else 4 if "Cfg<unsigned long, 7," in name else 6
+        assert min(512 // (-(-vgprs // 8) * 8), 163840 // max(lds, 1)) >= waves, (name[:120], vgprs, lds)
+        seen += 1
+    assert seen >= 30
