@@ -1034,7 +1034,7 @@ struct Ops {
   // 0.54 with it; as many distinct keys 0.450 and 0.456, 0.525 with a look before every
   // retry).
   template <bool LOOK = false>
-  __device__ static uint8_t upsert(const TableDev& tv, const Tile<T>& tile, K key, K val,
+  __device__ static __forceinline__ uint8_t upsert(const TableDev& tv, const Tile<T>& tile, K key, K val,
                                    int combine, int hot_row = -1) {
     return write<LOOK>(tv, tile, key, val, combine, false, hot_row);
   }
@@ -1043,7 +1043,7 @@ struct Ops {
   // share.  Callers pass a constant `erase`, so the other kind's code folds
   // away.
   template <bool LOOK = false>
-  __device__ static uint8_t write(const TableDev& tv, const Tile<T>& tile, K key, K val, int combine, bool erase,
+  __device__ static __forceinline__ uint8_t write(const TableDev& tv, const Tile<T>& tile, K key, K val, int combine, bool erase,
                                   int hot_row = -1) {
     if (key >= Keys<K>::FIRST_INVALID || (erase && tv.no_erase)) return ST_INVALID;
     if constexpr (C::CUCKOO) {

@@ -1,4 +1,5 @@
-"""What the compiler made of the kernels (CPU only): the persistent multi-table kernels
+"""What the compiler made of the kernels (CPU only): every device function is inlined
+(a call costs its kernel a stack in memory), and the persistent multi-table kernels
 have the registers and LDS for the occupancy that sizes their grids."""
 import os
 import re
@@ -37,23 +38,33 @@ def code_objects(so, tmp):
 
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
-    """name -> (VGPRs, LDS bytes) of every kernel."""
-    res = {}
+    """name -> (VGPRs, LDS bytes) of every kernel, and the functions that are none."""
+    res, other = {}, []
     for co in code_objects(hw.LIB_PATH, str(tmp_path_factory.mktemp("co"))):
-        text = subprocess.run([LLVM + "llvm-readelf", "--notes", co], capture_output=True, text=True,
+        text = subprocess.run([LLVM + "llvm-readelf", "-W", "-s", "--notes", co], capture_output=True, text=True,
                               check=True).stdout
+        funcs = set(re.findall(r" FUNC .* (\S+)$", text, re.M))
+        own = {}
         for doc in re.split(r"^  - \.ag", text, flags=re.M)[1:]:
             f = dict(re.findall(r"\.(name|vgpr_count|group_segment_fixed_size): +(\S+)$", doc, re.M))
-            res[f["name"]] = (int(f["vgpr_count"]), int(f["group_segment_fixed_size"]))
+            own[f["name"]] = (int(f["vgpr_count"]), int(f["group_segment_fixed_size"]))
+        assert own and set(own) <= funcs
+        res.update(own)
+        other += sorted(funcs - set(own))
     names = subprocess.run(["c++filt"], input="\n".join(res), capture_output=True, text=True, check=True).stdout.split("\n")
-    return dict(zip(names, res.values()))
+    return dict(zip(names, res.values())), other
+
+
+def test_no_device_function_is_called(kernels):
+    assert len(kernels[0]) > 100
+    assert kernels[1] == []
 
 
 def test_multi_table_kernels_meet_their_occupancy(kernels):
     """Waves per SIMD: as many as registers (512 per lane, granules of 8) and LDS (160 KB,
     blocks of one wave per SIMD) allow, at least the kernel's target."""
     seen = 0
-    for name, (vgprs, lds) in kernels.items():
+    for name, (vgprs, lds) in kernels[0].items():
         if "k_multi<" not in name:
             continue
         solo = re.search(r"k_multi<hw::Solo<.*, (\d+)> ?>\(", name)
