@@ -432,8 +432,9 @@ bool bad_ptr(const void* p) { return p == nullptr; }
 // scratch memory stays bounded (about 50 bytes per operation).
 constexpr uint64_t BULK_CHUNK = 1ull << 27;
 
-// Blocks of k_bulk_write at work at a time: six a CU.
+// Blocks of k_bulk_write at work at a time: six a CU; and how many fill the chip.
 constexpr uint64_t BULK_RESIDENT = 1536;
+constexpr uint32_t BULK_FILL = 512;
 
 // Room for a bin that receives `mean` operations on average: seven standard
 // deviations of a random spread; keys that are spread worse overflow into the
@@ -483,7 +484,7 @@ bool bulk_plan(const BulkShape& t, uint64_t n, bool erase, bool member, BulkPlan
   while ((2u << shift) * B <= (uint32_t)t.ks->bulk_slots) ++shift;
   auto fits = [&](uint32_t sh) { return bulk_room(per_bucket * (double)(1u << sh)) <= (uint32_t)BULK_CAP; };
   // as many buckets as a block takes, but enough blocks to fill the chip
-  while (shift > 0 && (!fits(shift) || (!member && ((nbh - 1) >> shift) + 1 < 512 && per_bucket * (double)(1u << shift) > 256)))
+  while (shift > 0 && (!fits(shift) || (!member && ((nbh - 1) >> shift) + 1 < BULK_FILL && per_bucket * (double)(1u << shift) > 256)))
     --shift;
   if (!fits(shift)) return false;
   p->shift = shift;
@@ -495,12 +496,16 @@ bool bulk_plan(const BulkShape& t, uint64_t n, bool erase, bool member, BulkPlan
   // Iceberg inserts: no more tiles choose between two backyard buckets at a time than
   // there are backyard buckets, as in a plain call, where such choices are spread
   // over the call's time.  All at once they meet equal fills and take the first choice
-  // (a fill of 2^20 slots to 0.9: 2.89 lines per query, not 2.96), and the fills are a little
-  // less even.  That fill takes 364 us, 221 without the limit, 870 with half the
-  // tiles, 590 plain; 2^22 slots 446, 377, 620, 1182.
+  // (ICEBERG, 2^20 slots filled to 0.9 in one call: 2.91 lines per query with all tiles,
+  // 2.95 with the limit, 2.96 plain; 202, 308 and 582 us).  Calls of few blocks take
+  // twice as many tiles: with the limit they were slower than plain calls in nearly full
+  // tables (2^15 slots from 0.75 to 0.95: 149 us plain, 188 with the limit, 156 so),
+  // and their choices are few (the standard deviation of the backyard's fills is 0.95 in all three).
   p->slow_tiles = BULK_THREADS;
-  if (!erase && design_iceberg(t.design))
-    p->slow_tiles = (uint32_t)std::min<uint64_t>(BULK_THREADS, t.backs / std::min<uint64_t>(p->parts, BULK_RESIDENT) + 1);
+  if (!erase && design_iceberg(t.design)) {
+    const uint64_t blocks = std::min<uint64_t>(p->parts, BULK_RESIDENT);
+    p->slow_tiles = (uint32_t)std::min<uint64_t>(BULK_THREADS, t.backs * (member || p->parts >= BULK_FILL ? 1 : 2) / blocks + 1);
+  }
   p->sub = 0;
   p->levels = p->parts <= (uint32_t)BULK_BINS ? 1 : 2;
   if (p->levels == 2) {

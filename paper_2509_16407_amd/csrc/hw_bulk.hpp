@@ -712,6 +712,7 @@ __device__ __forceinline__ void bulk_part(const TableDev& tv, BulkLds<C, ERASE> 
       const uint32_t tag = C::TAGS ? tag_of((uint64_t)k) : 0u;
       uint8_t s;
       if constexpr (ERASE) s = O::erase_locked(tv, tile, h, k, tag);
+      else if (C::ICEBERG && !erased) s = O::upsert_iceberg_backyard(tv, tile, h, k, L.vals[i], tag, combine);
       else s = O::template upsert_locked<true>(tv, tile, h, k, L.vals[i], tag, combine);
       if (tile.leader()) L.state[i] = s;
     };

@@ -1193,12 +1193,15 @@ struct Ops {
   // Iceberg insert under the front bucket's lock: the front bucket if it has a
   // free slot (after checking the backyard for the key once an erase has
   // happened), else the less loaded backyard choice, ties to the first.
-  template <bool EXCL>
+  // FRONT false: the caller has found the front bucket full and without the key.
+  template <bool EXCL, bool FRONT = true>
   __device__ static uint8_t upsert_iceberg_locked(const TableDev& tv, const Tile<T>& tile,
                                                   const Home& h, K key, K val, uint32_t tag,
                                                   int combine) {
     if (tile.leader()) probe_add(tv, PC_WRITE, 1);
-    BucketScan<K> rf = scan<true>(tv, tile, h.b1, key, tag);
+    BucketScan<K> rf;
+    rf.free = rf.hit = -1;
+    if constexpr (FRONT) rf = scan<true>(tv, tile, h.b1, key, tag);
     if (tile.leader()) probe_add(tv, PC_VISIT, 1);
     if (rf.hit >= 0) {
       combine_at(tv, tile, (uint64_t)h.b1 * B + rf.hit, val, combine);
@@ -1228,6 +1231,13 @@ struct Ops {
     if (rf.free >= 0 && claim_in_bucket(tv, tile, h.b1, rf, key, val, tag, EXCL) >= 0) return ST_DONE;
     if (h.b3 == h.h2) return claim_in_bucket(tv, tile, h.h2, r1, key, val, tag) >= 0 ? ST_DONE : ST_FULL;
     return claim_less_loaded(tv, tile, h.h2, r1, h.b3, r2, key, val, tag);
+  }
+
+  // The same for a key whose front bucket its caller, holding the lock, has found full
+  // and without it, in a table that has not erased.
+  __device__ static uint8_t upsert_iceberg_backyard(const TableDev& tv, const Tile<T>& tile, const Home& h, K key,
+                                                    K val, uint32_t tag, int combine) {
+    return upsert_iceberg_locked<true, false>(tv, tile, h, key, val, tag, combine);
   }
 
   // Lock-free query (Section 4.2).  Returns ST_DONE/ST_MISS/ST_INVALID, value in *out.
