@@ -453,32 +453,43 @@ BulkShape bulk_shape(const hwave_table* t) {
                    t->la.tv.nb_front, t->la.tv.nb_back};
 }
 
-// Fewest operations per home slot for which a call is grouped, in percent.  Plain
-// against grouped, microseconds, tables of 2^18 and 2^25 slots filled to 0.85,
-// upserts of present keys except where noted:
-//   tags:                0.11 per slot: ICEBERG_M 58 / 25; P2HT(M) erases of 0.125 142 / 54 (2^21), 708 /
-//                        312 (0.05: 32 / 29 and inserts 45 / 49)
-//   32-bit keys:         0.21: 56 / 26, 906 / 446; 0.11: 29 / 26, inserts 44 / 44
-//   64-bit, no tags:     DOUBLE 0.43: 56 / 31, 3581 / 1826 (0.85); 0.21: 42 / 29, inserts 52 / 53;
-//                        ICEBERG 0.21: 115 / 43 (2^19), 1485 / 630; P2HT erases of 0.125 96 / 89
-//                        (2^21), 233 / 238 (2^23)
-//   chaining, upserts:   whole chains are walked under the lock by one tile: 0.74: 74 / 44, 0.37:
-//                        44 / 34, inserts 51 / 46 (2^18) and 66 / 75 (2^19); erases go in parallel
-uint64_t bulk_min_percent(const BulkShape& t, bool erase) {
-  if (design_tags(t.design)) return 10;
-  if (design_chain(t.design)) return erase ? 25 : 60;
-  if (t.kv_bits == 32) return 16;
-  return t.design == HWAVE_ICEBERG ? 12 : 25;
+// What a grouped call does: KEEP upserts are inserts, which mostly bring absent keys.
+enum BulkKind { BULK_INSERT, BULK_UPSERT, BULK_ERASE };
+BulkKind bulk_kind(int combine) { return combine == HWAVE_KEEP ? BULK_INSERT : BULK_UPSERT; }
+
+// Fewest operations per home slot for which a call is grouped, in percent: where every
+// kind of such a call (into an empty table, to loads of 0.85 and 0.95, of present keys;
+// erases of present and of absent keys) is within 5% of the plain call or faster, in tables of 2^12
+// to 2^25 slots.  Plain against grouped, microseconds, below the line and at it:
+//   tags, 32 slots:      inserts and upserts 0.10: 36 / 30 (2^15), 317 / 308 (2^25, present keys);
+//                        ICEBERG_M to 0.95, 0.10 to 0.12: 89 / 104 (2^18), 99 / 91 (2^17)
+//   tags, 16 slots:      0.10: DOUBLE_M present 27 / 30 (2^15), P2HT(M) erases of absent keys 21 / 23;
+//                        0.13: 32 / 29, 24 / 23
+//   32-bit keys:         8 slots 0.16: present 25 / 30 (2^15); 0.21: 30 / 29.  16 and more 0.16: 31 / 29
+//   64-bit, no tags:     DOUBLE 0.25: inserts to 0.95 69 / 84 (2^16), present 25 / 30 (2^14), but 2^13
+//                        fresh 32 / 27; 0.29: 73 / 73, 28 / 29.  Erases 0.25: absent 30 / 41, 0.29
+//                        present 30 / 34 (2^13); 0.33 35 / 35.  ICEBERG inserts to 0.97, 0.12 of the slots: 216 / 255
+//                        (2^21); upserts of present keys 115 / 43 (0.21, 2^19)
+//   chaining:            erases of absent keys 0.29: 20 / 26 (2^14), 0.37: 24 / 25; upserts walk whole
+//                        chains under the lock with one tile: 0.69: 83 / 74 (2^19), inserts to 0.95 86 / 83
+uint64_t bulk_min_percent(const BulkShape& t, BulkKind kind) {
+  if (design_chain(t.design)) return kind == BULK_ERASE ? 33 : 60;
+  if (design_iceberg(t.design)) return kind != BULK_INSERT ? 12 : design_tags(t.design) ? 15 : 18;
+  if (design_tags(t.design)) return t.B < 32 ? 13 : 10;
+  if (t.kv_bits == 32) return t.B < 16 ? 21 : 16;
+  if (kind == BULK_ERASE) return 32;
+  return kind == BULK_INSERT && t.nbh * t.B <= 1u << 13 ? 25 : 29;
 }
 
 // How a call of n operations (at most BULK_CHUNK) is grouped (hw_bulk.hpp), or
 // false where one tile per operation is better.  `member`: as one of many tables of
 // a call, which fill the chip together.
-bool bulk_plan(const BulkShape& t, uint64_t n, bool erase, bool member, BulkPlan* p) {
+bool bulk_plan(const BulkShape& t, uint64_t n, BulkKind kind, bool member, BulkPlan* p) {
+  const bool erase = kind == BULK_ERASE;
   if (!(erase ? t.ks->bulk_erase : t.ks->bulk_upsert) || n < (member ? 1 : BULK_MIN_OPS) || n > BULK_CHUNK) return false;
   const uint32_t B = t.B;
   const uint64_t nbh = t.nbh;
-  if (nbh == 0 || n * 100 < nbh * B * bulk_min_percent(t, erase)) return false;
+  if (nbh == 0 || n * 100 < nbh * B * bulk_min_percent(t, kind)) return false;
   const double per_bucket = (double)n / (double)nbh;
   uint32_t shift = 0;
   while ((2u << shift) * B <= (uint32_t)t.ks->bulk_slots) ++shift;
@@ -555,7 +566,7 @@ bool bulk_run(hwave_table* t, bool erase, const void* keys, const void* vals, ui
               void* scratch, uint64_t scratch_bytes, hipStream_t s, hipError_t* err) {
   BulkPlan p;
   const uint64_t piece = bulk_piece(n), w = t->cfg.kv_bits / 8;
-  if (!scratch || ((uintptr_t)scratch % ALIGN) || !bulk_plan(bulk_shape(t), piece, erase, false, &p) || p.bytes > scratch_bytes) return false;
+  if (!scratch || ((uintptr_t)scratch % ALIGN) || !bulk_plan(bulk_shape(t), piece, erase ? BULK_ERASE : bulk_kind(combine), false, &p) || p.bytes > scratch_bytes) return false;
   *err = hipSuccess;
   for (uint64_t at = 0; at < n && *err == hipSuccess; at += piece) {
     const uint64_t m = n - at < piece ? n - at : piece;
@@ -690,9 +701,9 @@ int hwave_upsert(hwave_table* t, const void* d_keys, const void* d_vals, uint64_
 int hwave_write_scratch(const hwave_table* t, hwave_op op, uint64_t n, hwave_combine combine, uint64_t* bytes) {
   if (!t || !bytes || (int)op < HWAVE_OP_INSERT || (int)op > HWAVE_OP_ERASE) return HWAVE_EINVAL;
   BulkPlan p;
-  const bool erase = op == HWAVE_OP_ERASE;
-  const bool grouped = n != 0 && (erase || upsert_groups(t, op == HWAVE_OP_INSERT ? (int)HWAVE_KEEP : (int)combine)) &&
-                       bulk_plan(bulk_shape(t), bulk_piece(n), erase, false, &p);
+  const int comb = op == HWAVE_OP_INSERT ? (int)HWAVE_KEEP : (int)combine;
+  const bool grouped = n != 0 && (op == HWAVE_OP_ERASE || upsert_groups(t, comb)) &&
+                       bulk_plan(bulk_shape(t), bulk_piece(n), op == HWAVE_OP_ERASE ? BULK_ERASE : bulk_kind(comb), false, &p);
   *bytes = grouped ? p.bytes : 0;
   return HWAVE_OK;
 }
@@ -1247,7 +1258,7 @@ bool group_plan(const hwave_multi* m, const uint64_t* offsets, int combine, std:
     j.n = (uint32_t)(offsets[i + 1] - offsets[i]);
     j.begin = offsets[i];
     if (j.n == 0) continue;
-    if (bulk_plan(m->shapes[i], j.n, false, true, &j.plan)) grouped += j.n;
+    if (bulk_plan(m->shapes[i], j.n, bulk_kind(combine), true, &j.plan)) grouped += j.n;
     else j.plan = BulkPlan{};
     jobs->push_back(j);
   }
