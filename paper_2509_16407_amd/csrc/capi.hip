@@ -447,10 +447,11 @@ struct BulkShape {
   hwave_design design;
   uint32_t kv_bits, B;  // B: slot units per home bucket
   uint64_t nbh, backs;  // home buckets; iceberg's backyard buckets
+  bool stable;          // the table never erases
 };
 BulkShape bulk_shape(const hwave_table* t) {
   return BulkShape{t->ks, t->design, t->cfg.kv_bits, design_chain(t->design) ? 8u : t->cfg.bucket_slots,
-                   t->la.tv.nb_front, t->la.tv.nb_back};
+                   t->la.tv.nb_front, t->la.tv.nb_back, t->la.tv.no_erase != 0};
 }
 
 // What a grouped call does: KEEP upserts are inserts, which mostly bring absent keys.
@@ -487,6 +488,10 @@ uint64_t bulk_min_percent(const BulkShape& t, BulkKind kind) {
 bool bulk_plan(const BulkShape& t, uint64_t n, BulkKind kind, bool member, BulkPlan* p) {
   const bool erase = kind == BULK_ERASE;
   if (!(erase ? t.ks->bulk_erase : t.ks->bulk_upsert) || n < (member ? 1 : BULK_MIN_OPS) || n > BULK_CHUNK) return false;
+  // In a table that never erases, a plain upsert of a present key takes no lock: one look
+  // and one atomic, which grouping cannot beat (DOUBLE_M, 0.2 operations per slot: 11 us plain
+  // against 30 grouped in 2^15 slots, 421 against 576 in 2^25; ICEBERG_M 11 / 47 in 2^17).
+  if (!erase && t.stable) return false;
   const uint32_t B = t.B;
   const uint64_t nbh = t.nbh;
   if (nbh == 0 || n * 100 < nbh * B * bulk_min_percent(t, kind)) return false;

@@ -1,5 +1,7 @@
-"""Which single-table calls are grouped by bucket: the smallest share of a table's slots per
-design, bucket and kind of call."""
+"""Which calls are grouped by bucket: the smallest share of a table's slots per design,
+bucket and kind of call; tables that never erase keep the plain call."""
+import ctypes
+
 import pytest
 
 import paper_2509_16407_amd as hw
@@ -22,3 +24,16 @@ def test_least_share_of_the_slots(design, bits, bucket, tile, kind, cap, below, 
     t = hw.Table(cap, design, kv_bits=bits, bucket=bucket, tile=tile)
     grouped = lambda per: t._scratch(hw.OPS[kind], int(per * cap), hw.COMBINES["keep" if kind == "insert" else "sum"], None) is not None
     assert not grouped(below) and grouped(above)
+
+
+@pytest.mark.parametrize("design", ["DOUBLE", "DOUBLE_M", "ICEBERG", "ICEBERG_M", "CHAINING"])
+def test_tables_that_never_erase_keep_the_plain_call(design):
+    """Their plain upserts of present keys take no lock."""
+    cap, n = 1 << 16, 60000
+    mk = lambda flags: [hw.Table(cap, design, flags=flags) for _ in range(2)]
+    for flags in (0, hw.F_NO_ERASE):
+        ts = mk(flags)
+        for op, c in (("insert", 1), ("upsert", 0), ("upsert", 2)):
+            assert (ts[0]._scratch(hw.OPS[op], n, c, None) is not None) == (flags == 0)
+        m = hw.Multi(ts)
+        assert (m._scratch((ctypes.c_uint64 * 3)(0, n, 2 * n), 2 * n, 0, None) is not None) == (flags == 0)
