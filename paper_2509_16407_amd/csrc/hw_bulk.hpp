@@ -252,6 +252,21 @@ __device__ __forceinline__ uint32_t nth_bit(Mask m, uint32_t n) {
   return (uint32_t)__ffsll((unsigned long long)m) - 1;
 }
 
+// Merges an operation's value into the one (in LDS) of its key's first operation.
+template <typename K>
+__device__ __forceinline__ void merge_value(K* to, K v, int combine) {
+  if (combine == C_SUM) __hip_atomic_fetch_add(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else if (combine == C_MIN) __hip_atomic_fetch_min(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else if (combine == C_MAX) __hip_atomic_fetch_max(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  else if (combine == C_REPLACE) __hip_atomic_store(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// An operation's status, given that of its key's first one.
+template <bool ERASE>
+__device__ __forceinline__ uint8_t follow(uint8_t s, bool first) {
+  return first || s != ST_DONE ? s : ERASE ? (uint8_t)ST_MISS : (uint8_t)ST_EXISTED;
+}
+
 // Which elements of bucket b of the part's image equal x (a tag or a key; the first
 // n of them are looked at where they are keys).
 template <class Lds, typename X>
@@ -446,16 +461,8 @@ __device__ __forceinline__ void bulk_part(const TableDev& tv, BulkLds<C, ERASE> 
       }
       e = (e + 1) & (hash_n - 1);
     }
-    if constexpr (!ERASE) {
-      if (lead[r] != i) {
-        K* lv = &L.vals[lead[r]];
-        const K v = L.vals[i];
-        if (combine == C_SUM) __hip_atomic_fetch_add(lv, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        else if (combine == C_MIN) __hip_atomic_fetch_min(lv, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        else if (combine == C_MAX) __hip_atomic_fetch_max(lv, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        else if (combine == C_REPLACE) __hip_atomic_store(lv, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
-    }
+    if constexpr (!ERASE)
+      if (lead[r] != i) merge_value(&L.vals[lead[r]], L.vals[i], combine);
   }
   __syncthreads();  // the locks' answers have arrived: reads below come after them; the merge table is done with
 
@@ -742,12 +749,7 @@ __device__ __forceinline__ void bulk_part(const TableDev& tv, BulkLds<C, ERASE> 
   for (int r = 0; r < PER; ++r) {
     const uint32_t i = r * BULK_THREADS + tid;
     if (i >= count) continue;
-    uint8_t s = L.state[lead[r]];
-    if (lead[r] != i) {
-      if constexpr (ERASE) s = s == ST_DONE ? (uint8_t)ST_MISS : s;
-      else s = s == ST_DONE ? (uint8_t)ST_EXISTED : s;
-    }
-    stat[i] = s;
+    stat[i] = follow<ERASE>(L.state[lead[r]], lead[r] == i);
   }
 }
 
@@ -785,16 +787,25 @@ k_bulk_back(uint32_t bins, uint32_t cap, const uint32_t* __restrict__ count, con
 // or BULK_PENDING) through the per-tile path, in that order.
 //
 // bulk_finish: 64 operations from `base` on, by one wave; pos null: none is decided.
+//
+// What is left over of a skewed call is its hot keys, closer together than in the call
+// itself, so equal keys of the 64 merge first: one locked operation each.  Without that, the
+// waits for a hot key's lock took longer than in a plain call (27,852 upserts, half of them of one
+// key, DOUBLE, 2^15 slots: 30 ms plain, 34 unmerged, 0.79 so).
 template <class C, bool ERASE>
 __device__ __forceinline__ void bulk_finish(const TableDev& tv, const typename C::K* __restrict__ keys,
                                             const typename C::K* __restrict__ vals, uint64_t base, uint64_t n,
                                             const uint32_t* __restrict__ pos, const uint8_t* __restrict__ stat,
                                             int combine, uint8_t* __restrict__ out) {
-  __shared__ uint8_t order_lds[BLOCK];
   using K = typename C::K;
+  struct Rest {
+    K key[64], val[64];  // val: of the first of equal keys, all of theirs
+    uint8_t order[64], stat[64];
+  };
+  __shared__ Rest rest_lds[BLOCK / 64];
   const Tile<C::T> tile;
   const uint32_t lane = __lane_id();
-  uint8_t* order = order_lds + __builtin_amdgcn_readfirstlane(threadIdx.x / 64) * 64;
+  Rest& L = rest_lds[__builtin_amdgcn_readfirstlane(threadIdx.x / 64)];
   bool rest = false;
   if (base + lane < n) {
     const uint32_t p = pos ? pos[base + lane] : BULK_NONE;
@@ -804,17 +815,39 @@ __device__ __forceinline__ void bulk_finish(const TableDev& tv, const typename C
   }
   const uint64_t m = __ballot(rest);
   if (m == 0) return;
-  if (rest) order[__popcll(m & ((1ull << lane) - 1))] = (uint8_t)lane;
-  wave_sync();
-  const uint32_t cnt = (uint32_t)__popcll(m);
-  for (uint32_t u = lane / C::T; u < cnt; u += 64 / C::T) {
-    const uint64_t j = base + order[u];
-    const K key = keys[j];
-    uint8_t s;
-    if constexpr (ERASE) s = Ops<C>::erase(tv, tile, key);
-    else s = Ops<C>::upsert(tv, tile, key, vals[j], combine);
-    if (out && tile.leader()) out[j] = s;
+  K key = 0, val = 0;
+  if (rest) {
+    key = keys[base + lane];
+    if constexpr (!ERASE) val = vals[base + lane];
   }
+  uint32_t lead = lane;  // the first lane with the same key
+  for (uint64_t todo = m; todo;) {
+    const uint32_t f = (uint32_t)ffs64(todo);
+    const K kf = __shfl(key, (int)f, 64);
+    const uint64_t same = __ballot(rest && key == kf);
+    if (same >> lane & 1) lead = f;
+    todo &= ~same;
+  }
+  const uint64_t leads = __ballot(rest && lead == lane);
+  if (rest && lead == lane) {
+    L.order[__popcll(leads & ((1ull << lane) - 1))] = (uint8_t)lane;
+    L.key[lane] = key;
+    if constexpr (!ERASE) L.val[lane] = val;
+  }
+  wave_sync();
+  if constexpr (!ERASE)
+    if (rest && lead != lane) merge_value(&L.val[lead], val, combine);
+  wave_sync();
+  const uint32_t cnt = (uint32_t)__popcll(leads);
+  for (uint32_t u = lane / C::T; u < cnt; u += 64 / C::T) {
+    const uint32_t o = L.order[u];
+    uint8_t s;
+    if constexpr (ERASE) s = Ops<C>::erase(tv, tile, L.key[o]);
+    else s = Ops<C>::upsert(tv, tile, L.key[o], L.val[o], combine);
+    if (tile.leader()) L.stat[o] = s;
+  }
+  wave_sync();
+  if (rest && out) out[base + lane] = follow<ERASE>(L.stat[lead], lead == lane);
   wave_sync();
 }
 
