@@ -267,6 +267,13 @@ __device__ __forceinline__ uint8_t follow(uint8_t s, bool first) {
   return first || s != ST_DONE ? s : ERASE ? (uint8_t)ST_MISS : (uint8_t)ST_EXISTED;
 }
 
+// Instrumented builds: an upsert that its home bucket decided (others are counted where
+// they search).
+__device__ __forceinline__ void count_home_write(const TableDev& tv) {
+  probe_add(tv, PC_WRITE, 1);
+  probe_add(tv, PC_VISIT, 1);
+}
+
 // Which elements of bucket b of the part's image equal x (a tag or a key; the first
 // n of them are looked at where they are keys).
 template <class Lds, typename X>
@@ -544,6 +551,7 @@ __device__ __forceinline__ void bulk_part(const TableDev& tv, BulkLds<C, ERASE> 
       L.op_of[s] = (uint16_t)BULK_NO_OP;
       L.state[o] = ST_EXISTED;
       O::combine_lane(tv, slot0 + s, L.vals[o], combine);
+      count_home_write(tv);
     }
   }
   if constexpr (ERASE && C::TAGS) wait_mem();  // the keys are gone before their tags are
@@ -574,6 +582,7 @@ __device__ __forceinline__ void bulk_part(const TableDev& tv, BulkLds<C, ERASE> 
           } else {
             s = ST_EXISTED;
             O::combine_lane(tv, s0 + j, L.vals[i], combine);
+            count_home_write(tv);
           }
         }
       }
@@ -596,12 +605,6 @@ __device__ __forceinline__ void bulk_part(const TableDev& tv, BulkLds<C, ERASE> 
         }
       }
     }
-#ifdef HW_INSTRUMENT
-    if (!ERASE && (s == ST_EXISTED || s == BULK_NEW)) {
-      probe_add(tv, PC_WRITE, 1);
-      probe_add(tv, PC_VISIT, 1);
-    }
-#endif
     if (ALTERNATE && s == BULK_SLOW) {
       const uint32_t at = __hip_atomic_fetch_add(n_slow_lds, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       L.list[at] = (uint16_t)i;
@@ -690,6 +693,7 @@ __device__ __forceinline__ void bulk_part(const TableDev& tv, BulkLds<C, ERASE> 
       if constexpr (C::TAGS && C::ICEBERG) st((uint16_t*)tv.tagw + slot0 + s, (uint16_t)tag_of((uint64_t)L.keys[o]));
       if constexpr (C::TAGS || C::ICEBERG || C::CHAIN || sizeof(K) == 8) O::publish(tv, slot0 + s, L.keys[o], L.vals[o]);
       L.state[o] = ST_DONE;
+      count_home_write(tv);
     }
     wait_mem();
     __syncthreads();
