@@ -1,7 +1,8 @@
 """Builds libhashwave.so for gfx950 in-tree: each source compiled by hipcc in
 parallel, then linked into one shared library next to this file.  Also builds
 libhashwave_instr.so, the same sources with -DHW_INSTRUMENT (query probe
-counters, hwave_probe_counters), used by tests that count lines per query."""
+counters, hwave_probe_counters) and small pieces of grouped calls, used by tests that
+count lines per query or reach a piece's edges."""
 from __future__ import annotations
 
 import concurrent.futures as cf
@@ -48,7 +49,7 @@ def build(extra_flags=(), out: str = OUT, jobs: int | None = None, instrumented:
     """Compiles every source (always) and links `out`; with `instrumented`, also
     the instrumented library.  Returns the path of `out`."""
     if instrumented:
-        _link(list(extra_flags) + ["-DHW_INSTRUMENT"], OUT_INSTR, OBJ_INSTR, jobs)
+        _link(list(extra_flags) + ["-DHW_INSTRUMENT", "-DHW_BULK_CHUNK=(1ull<<18)"], OUT_INSTR, OBJ_INSTR, jobs)
     return _link(list(extra_flags), out, OBJ, jobs)
 
 

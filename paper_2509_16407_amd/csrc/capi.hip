@@ -428,9 +428,13 @@ int init_table(hwave_table* t, void* base, uint64_t bytes, const Layout& L, hwav
 
 bool bad_ptr(const void* p) { return p == nullptr; }
 
-// Most operations grouped in one go: larger calls run in equal pieces, so the
-// scratch memory stays bounded (about 50 bytes per operation).
-constexpr uint64_t BULK_CHUNK = 1ull << 27;
+// Most operations grouped in one go: larger calls run in pieces, one after another in the
+// same scratch memory, which so stays bounded (about 50 bytes per operation).  The
+// instrumented build has smaller pieces: tests reach their edges there.
+#ifndef HW_BULK_CHUNK
+#define HW_BULK_CHUNK (1ull << 27)
+#endif
+constexpr uint64_t BULK_CHUNK = HW_BULK_CHUNK;
 
 // Blocks of k_bulk_write at work at a time: six a CU; and how many fill the chip.
 constexpr uint64_t BULK_RESIDENT = 1536;
@@ -1240,41 +1244,33 @@ int hwave_multi_upsert(hwave_multi* m, const uint64_t* h_offsets, const void* d_
 
 namespace {
 
-// A group's upsert, grouped by bucket (hw_bulk.hpp): the jobs and, per step, the blocks
-// before each job's.  False where one tile per operation is better: few operations, or
-// most of them in tables that get too few; and for tables of different configurations.
-//
-// One tile per operation against grouped, microseconds, 32-bit DOUBLE tables filled to
-// 0.85: 40 of 2^12 slots 360 / 65, 400 of 2^10 370 / 129, 4 of 2^20 658 / 216, 20 of 2^20 with 1.7
-// operations per slot 5125 / 1714; ICEBERG_M, 64-bit, 10 of 2^13 564 / 125, 20 of 2^20 5265 / 2041.
-bool group_plan(const hwave_multi* m, const uint64_t* offsets, int combine, std::vector<BulkJob>* jobs,
-                std::vector<uint32_t>* first, GroupArgs* a, uint64_t* bytes) try {
-  if (m->menu != MENU_SOLO || !m->shapes[0].ks->group_upsert || (m->agg && combine != HWAVE_REPLACE)) return false;
-  uint64_t total = 0, grouped = 0;
-  for (uint32_t i = 0; i < m->n_tables; i++) {
-    if (offsets[i + 1] < offsets[i]) return false;
-    total += offsets[i + 1] - offsets[i];
-  }
-  if (total < BULK_MIN_OPS || total > 0xFFFFFFFFull) return false;
-  for (uint32_t i = 0; i < m->n_tables; i++) {
-    BulkJob j{};
-    j.home = m->homes[i];
-    j.table = i;
-    j.n = (uint32_t)(offsets[i + 1] - offsets[i]);
-    j.begin = offsets[i];
-    if (j.n == 0) continue;
-    if (bulk_plan(m->shapes[i], j.n, bulk_kind(combine), true, &j.plan)) grouped += j.n;
-    else j.plan = BulkPlan{};
-    jobs->push_back(j);
-  }
-  if (2 * grouped < total) return false;
-  const uint32_t n = (uint32_t)jobs->size();
-  first->assign((size_t)GROUP_STEPS * n, 0);
-  uint64_t at = round_up(n * sizeof(BulkJob), ALIGN) + round_up(first->size() * 4, ALIGN);
-  uint64_t blocks[GROUP_STEPS] = {};
+// A group's upsert, grouped by bucket (hw_bulk.hpp), as runs of consecutive tables of at
+// most BULK_CHUNK operations (a larger table in pieces): one after another on the
+// stream, all in the same scratch memory.
+struct GroupRun {
+  size_t job;                 // first of its jobs
+  uint32_t n;                 // jobs
+  size_t list;                // offset of its list in the staging buffer: jobs, then `first`
+  std::vector<uint32_t> first;  // per step, the blocks before each job's
+  GroupArgs args;
+  size_t first_at() const { return round_up(n * sizeof(BulkJob), ALIGN); }
+  size_t list_bytes() const { return first_at() + round_up(first.size() * 4, ALIGN); }
+};
+struct GroupPlan {
+  std::vector<BulkJob> jobs;
+  std::vector<GroupRun> runs;
+  uint64_t bytes = 0;  // scratch memory: the largest run's
+  size_t staged = 0;   // bytes of all runs' lists
+};
+
+// Lays out a run's lists, blocks and scratch memory; false for more blocks than a launch takes.
+bool group_run_layout(GroupPlan* g, GroupRun* r) {
+  const uint32_t n = r->n;
+  r->first.assign((size_t)GROUP_STEPS * n, 0);
+  uint64_t at = r->list_bytes(), blocks[GROUP_STEPS] = {};
   constexpr uint64_t TILE = (uint64_t)BULK_SPLIT_THREADS * GROUP_PER;
   for (uint32_t i = 0; i < n; i++) {
-    BulkJob& j = (*jobs)[i];
+    BulkJob& j = g->jobs[r->job + i];
     const BulkPlan& p = j.plan;
     const bool on = p.levels != 0, two = p.levels == 2;
     const uint64_t step[GROUP_STEPS] = {on ? (p.zero_bytes + GROUP_ZERO_BYTES - 1) / GROUP_ZERO_BYTES : 0,
@@ -1284,18 +1280,64 @@ bool group_plan(const hwave_multi* m, const uint64_t* offsets, int combine, std:
                                         two ? (uint64_t)p.bins * ((p.cap1 + 255) / 256) : 0,
                                         ((uint64_t)j.n + GROUP_FINISH_OPS - 1) / GROUP_FINISH_OPS};
     for (int k = 0; k < GROUP_STEPS; k++) {
-      (*first)[(size_t)k * n + i] = (uint32_t)blocks[k];
+      r->first[(size_t)k * n + i] = (uint32_t)blocks[k];
       blocks[k] += step[k];
     }
     j.scratch = at;
     at += p.bytes;
   }
   for (int k = 0; k < GROUP_STEPS; k++) {
-    if (blocks[k] > 0x7FFFFFFFull) return false;
-    a->blocks[k] = (uint32_t)blocks[k];
+    // a launch takes fewer than 2^32 threads
+    if (blocks[k] >= (1ull << 32) / BULK_SPLIT_THREADS) return false;
+    r->args.blocks[k] = (uint32_t)blocks[k];
   }
-  a->n = total;
-  *bytes = at;
+  r->list = g->staged;
+  g->staged += r->list_bytes();
+  g->bytes = std::max(g->bytes, at);
+  return true;
+}
+
+// The runs of a call; false where one tile per operation is better: few operations, or
+// most of them in tables that get too few; and for tables of different configurations.
+//
+// One tile per operation against grouped, microseconds, 32-bit DOUBLE tables filled to
+// 0.85: 40 of 2^12 slots 360 / 65, 400 of 2^10 370 / 129, 4 of 2^20 658 / 216, 20 of 2^20 with 1.7
+// operations per slot 5125 / 1714; ICEBERG_M, 64-bit, 10 of 2^13 564 / 125, 20 of 2^20 5265 / 2041.
+bool group_plan(const hwave_multi* m, const uint64_t* offsets, int combine, GroupPlan* g) try {
+  if (m->menu != MENU_SOLO || !m->shapes[0].ks->group_upsert || (m->agg && combine != HWAVE_REPLACE)) return false;
+  uint64_t total = 0, grouped = 0;
+  for (uint32_t i = 0; i < m->n_tables; i++) {
+    if (offsets[i + 1] < offsets[i]) return false;
+    total += offsets[i + 1] - offsets[i];
+  }
+  if (total < BULK_MIN_OPS) return false;
+  uint64_t in_run = 0;
+  for (uint32_t i = 0; i < m->n_tables; i++) {
+    const uint64_t n = offsets[i + 1] - offsets[i];
+    if (n == 0) continue;
+    const uint64_t piece = bulk_piece(n);
+    BulkPlan plan{};
+    if (bulk_plan(m->shapes[i], piece, bulk_kind(combine), true, &plan)) grouped += n;
+    else plan = BulkPlan{};
+    for (uint64_t at = 0; at < n; at += piece) {
+      BulkJob j{};
+      j.plan = plan;
+      j.home = m->homes[i];
+      j.table = i;
+      j.n = (uint32_t)std::min(piece, n - at);
+      j.begin = offsets[i] + at;
+      if (g->runs.empty() || in_run + j.n > BULK_CHUNK) {
+        g->runs.push_back(GroupRun{g->jobs.size(), 0, 0, {}, {}});
+        in_run = 0;
+      }
+      in_run += j.n;
+      g->runs.back().n++;
+      g->jobs.push_back(j);
+    }
+  }
+  if (2 * grouped < total) return false;
+  for (GroupRun& r : g->runs)
+    if (!group_run_layout(g, &r)) return false;
   return true;
 } catch (const std::bad_alloc&) {
   return false;
@@ -1307,10 +1349,8 @@ extern "C" {
 
 int hwave_multi_scratch(const hwave_multi* m, const uint64_t* h_offsets, hwave_combine combine, uint64_t* bytes) {
   if (!m || !h_offsets || !bytes || (int)combine < HWAVE_SUM || (int)combine > HWAVE_MAX) return HWAVE_EINVAL;
-  std::vector<BulkJob> jobs;
-  std::vector<uint32_t> first;
-  GroupArgs a;
-  if (!group_plan(m, h_offsets, (int)combine, &jobs, &first, &a, bytes)) *bytes = 0;
+  GroupPlan g;
+  *bytes = group_plan(m, h_offsets, (int)combine, &g) ? g.bytes : 0;
   return HWAVE_OK;
 }
 
@@ -1318,32 +1358,30 @@ int hwave_multi_upsert_scratch(hwave_multi* m, const uint64_t* h_offsets, const 
                                hwave_combine combine, uint8_t* d_status, void* d_scratch, uint64_t scratch_bytes,
                                void* stream) {
   if (!m || !h_offsets || (int)combine < HWAVE_SUM || (int)combine > HWAVE_MAX) return HWAVE_EINVAL;
-  std::vector<BulkJob> jobs;
-  std::vector<uint32_t> first;
-  GroupArgs a;
-  uint64_t bytes = 0;
+  GroupPlan g;
   if (!d_scratch || (uintptr_t)d_scratch % ALIGN || bad_ptr(d_keys) || bad_ptr(d_vals) ||
-      !group_plan(m, h_offsets, (int)combine, &jobs, &first, &a, &bytes) || bytes > scratch_bytes)
+      !group_plan(m, h_offsets, (int)combine, &g) || g.bytes > scratch_bytes)
     return hwave_multi_upsert(m, h_offsets, d_keys, d_vals, combine, d_status, stream);
-  // The jobs go to the scratch buffer through the staging buffer, which may still be
+  // The lists go to the scratch buffer through the staging buffer, which may still be
   // in flight from the previous call.
-  const size_t n = jobs.size(), at = round_up(n * sizeof(BulkJob), ALIGN), list = at + first.size() * 4;
-  const int rc = multi_reserve(m, list / sizeof(MultiItem) + 1);
+  const int rc = multi_reserve(m, g.staged / sizeof(MultiItem) + 1);
   if (rc) return rc;
-  if (m->staged_pending) {
-    hipError_t e = hipEventSynchronize(m->staged);
-    if (e != hipSuccess) return hip_fail(e);
-  }
-  memcpy(m->h_stage, jobs.data(), n * sizeof(BulkJob));
-  memcpy((uint8_t*)m->h_stage + at, first.data(), first.size() * 4);
+  hipError_t e = m->staged_pending ? hipEventSynchronize(m->staged) : hipSuccess;
   hipStream_t s = (hipStream_t)stream;
-  hipError_t e = hipMemcpyAsync(d_scratch, m->h_stage, list, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipEventRecord(m->staged, s);
-  if (e != hipSuccess) return hip_fail(e);
-  m->staged_pending = true;
-  a.g = BulkGroup{(const BulkJob*)d_scratch, (const uint32_t*)((uint8_t*)d_scratch + at), (uint32_t)n, (uint8_t*)d_scratch};
-  a.tables = m->d_tables;
-  e = m->shapes[0].ks->group_upsert(a, jobs.data(), d_keys, d_vals, (int)combine, d_status, s);
+  uint8_t* scratch = (uint8_t*)d_scratch;
+  for (size_t i = 0; i < g.runs.size() && e == hipSuccess; i++) {
+    GroupRun& r = g.runs[i];
+    uint8_t* stage = (uint8_t*)m->h_stage + r.list;
+    memcpy(stage, &g.jobs[r.job], r.n * sizeof(BulkJob));
+    memcpy(stage + r.first_at(), r.first.data(), r.first.size() * 4);
+    e = hipMemcpyAsync(scratch, stage, r.list_bytes(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipEventRecord(m->staged, s);
+    m->staged_pending = true;
+    r.args.g = BulkGroup{(const BulkJob*)scratch, (const uint32_t*)(scratch + r.first_at()), r.n, scratch};
+    r.args.tables = m->d_tables;
+    if (e == hipSuccess)
+      e = m->shapes[0].ks->group_upsert(r.args, &g.jobs[r.job], d_keys, d_vals, (int)combine, d_status, s);
+  }
   return e == hipSuccess ? HWAVE_OK : hip_fail(e);
 }
 

@@ -262,12 +262,11 @@ typedef hipError_t (*mixed_fn)(const LaunchArgs&, const uint8_t*, const void*, c
 typedef hipError_t (*bulk_fn)(const LaunchArgs&, const BulkPlan&, uint8_t*, const void*, const void*, uint32_t, int,
                               uint8_t*, hipStream_t);
 
-// One upsert per table of a group (hw_bulk.hpp): blocks[] per step, `lds` bytes for k_group_write.
+// One run of a group's upsert (hw_bulk.hpp): blocks[] per step.
 struct GroupArgs {
   BulkGroup g;
   const MultiTable* tables;
   uint32_t blocks[GROUP_STEPS];
-  uint64_t n;  // operations of all tables
 };
 typedef hipError_t (*group_fn)(const GroupArgs&, const BulkJob* host_jobs, const void*, const void*, int, uint8_t*,
                                hipStream_t);
@@ -362,12 +361,14 @@ struct Launch {
     }
     const K *k = (const K*)keys, *v = (const K*)vals;
     auto on = [&](int step) { return dim3(a.blocks[step]); };
-    hipLaunchKernelGGL((k_group_clear<K>), on(GROUP_ZERO), dim3(256), 0, s, a.g);
-    hipLaunchKernelGGL((k_group_split<K, false, GROUP_PER>), on(GROUP_SPLIT), dim3(BULK_SPLIT_THREADS), 0, s, a.g, k, v);
-    if (a.blocks[GROUP_SPLIT2])
-      hipLaunchKernelGGL((k_group_split<K, true, GROUP_PER>), on(GROUP_SPLIT2), dim3(BULK_SPLIT_THREADS), 0, s, a.g, k, v);
-    hipLaunchKernelGGL((k_group_write<C>), on(GROUP_WRITE), dim3(BULK_THREADS), lds, s, a.g, a.tables, combine);
-    if (a.blocks[GROUP_BACK]) hipLaunchKernelGGL((k_group_back<K>), on(GROUP_BACK), dim3(256), 0, s, a.g);
+    if (a.blocks[GROUP_WRITE]) {
+      hipLaunchKernelGGL((k_group_clear<K>), on(GROUP_ZERO), dim3(256), 0, s, a.g);
+      hipLaunchKernelGGL((k_group_split<K, false, GROUP_PER>), on(GROUP_SPLIT), dim3(BULK_SPLIT_THREADS), 0, s, a.g, k, v);
+      if (a.blocks[GROUP_SPLIT2])
+        hipLaunchKernelGGL((k_group_split<K, true, GROUP_PER>), on(GROUP_SPLIT2), dim3(BULK_SPLIT_THREADS), 0, s, a.g, k, v);
+      hipLaunchKernelGGL((k_group_write<C>), on(GROUP_WRITE), dim3(BULK_THREADS), lds, s, a.g, a.tables, combine);
+      if (a.blocks[GROUP_BACK]) hipLaunchKernelGGL((k_group_back<K>), on(GROUP_BACK), dim3(256), 0, s, a.g);
+    }
     hipLaunchKernelGGL((k_group_finish<C>), on(GROUP_FINISH), dim3(BLOCK), 0, s, a.g, a.tables, k, v, combine,
                        status);
     return hipGetLastError();
