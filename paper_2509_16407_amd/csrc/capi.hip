@@ -486,18 +486,27 @@ uint64_t bulk_min_percent(const BulkShape& t, BulkKind kind) {
   return kind == BULK_INSERT && t.nbh * t.B <= 1u << 13 ? 25 : 29;
 }
 
+// Whether an upsert of a table that never erases is grouped.  Its plain upserts of present keys
+// take no lock: one look and one atomic, which grouping beats only where several operations
+// meet in a key, and where memory or a launch's many tables bound the plain call.  Plain against grouped, microseconds, present
+// keys unless noted: DOUBLE_M 0.2 operations per slot 11 / 30 (2^15), 421 / 576 (2^25); 1.7 per slot 31 / 43 (2^18), 339 / 367
+// (2^22), 1478 / 1507 (2^24; fresh 2863 / 1619); CHAINING 1451 / 1720 (2^24).  Groups with 1.7 per
+// slot: 400 tables of 2^12 slots 294 / 195 (fresh 851 / 203), 40 of 2^10 48 / 50; ICEBERG_M 56 / 77.
+bool bulk_stable(const BulkShape& t, uint64_t n, uint64_t call) {
+  if (n < t.nbh * t.B || design_iceberg(t.design)) return false;
+  return call ? call >= 1u << 17 : !design_chain(t.design) && t.nbh * t.B >= 1u << 24;
+}
+
 // How a call of n operations (at most BULK_CHUNK) is grouped (hw_bulk.hpp), or
-// false where one tile per operation is better.  `member`: as one of many tables of
-// a call, which fill the chip together.
-bool bulk_plan(const BulkShape& t, uint64_t n, BulkKind kind, bool member, BulkPlan* p) {
+// false where one tile per operation is better.  `call`: the operations of all tables of a
+// group's call, which fill the chip together; 0 for a table's own call.
+bool bulk_plan(const BulkShape& t, uint64_t n, BulkKind kind, uint64_t call, BulkPlan* p) {
+  const bool member = call != 0;
   const bool erase = kind == BULK_ERASE;
   if (!(erase ? t.ks->bulk_erase : t.ks->bulk_upsert) || n < (member ? 1 : BULK_MIN_OPS) || n > BULK_CHUNK) return false;
-  // In a table that never erases, a plain upsert of a present key takes no lock: one look
-  // and one atomic, which grouping cannot beat (DOUBLE_M, 0.2 operations per slot: 11 us plain
-  // against 30 grouped in 2^15 slots, 421 against 576 in 2^25; ICEBERG_M 11 / 47 in 2^17).
-  if (!erase && t.stable) return false;
   const uint32_t B = t.B;
   const uint64_t nbh = t.nbh;
+  if (!erase && t.stable && !bulk_stable(t, n, call)) return false;
   if (nbh == 0 || n * 100 < nbh * B * bulk_min_percent(t, kind)) return false;
   const double per_bucket = (double)n / (double)nbh;
   uint32_t shift = 0;
@@ -575,7 +584,7 @@ bool bulk_run(hwave_table* t, bool erase, const void* keys, const void* vals, ui
               void* scratch, uint64_t scratch_bytes, hipStream_t s, hipError_t* err) {
   BulkPlan p;
   const uint64_t piece = bulk_piece(n), w = t->cfg.kv_bits / 8;
-  if (!scratch || ((uintptr_t)scratch % ALIGN) || !bulk_plan(bulk_shape(t), piece, erase ? BULK_ERASE : bulk_kind(combine), false, &p) || p.bytes > scratch_bytes) return false;
+  if (!scratch || ((uintptr_t)scratch % ALIGN) || !bulk_plan(bulk_shape(t), piece, erase ? BULK_ERASE : bulk_kind(combine), 0, &p) || p.bytes > scratch_bytes) return false;
   *err = hipSuccess;
   for (uint64_t at = 0; at < n && *err == hipSuccess; at += piece) {
     const uint64_t m = n - at < piece ? n - at : piece;
@@ -712,7 +721,7 @@ int hwave_write_scratch(const hwave_table* t, hwave_op op, uint64_t n, hwave_com
   BulkPlan p;
   const int comb = op == HWAVE_OP_INSERT ? (int)HWAVE_KEEP : (int)combine;
   const bool grouped = n != 0 && (op == HWAVE_OP_ERASE || upsert_groups(t, comb)) &&
-                       bulk_plan(bulk_shape(t), bulk_piece(n), op == HWAVE_OP_ERASE ? BULK_ERASE : bulk_kind(comb), false, &p);
+                       bulk_plan(bulk_shape(t), bulk_piece(n), op == HWAVE_OP_ERASE ? BULK_ERASE : bulk_kind(comb), 0, &p);
   *bytes = grouped ? p.bytes : 0;
   return HWAVE_OK;
 }
@@ -1317,7 +1326,7 @@ bool group_plan(const hwave_multi* m, const uint64_t* offsets, int combine, Grou
     if (n == 0) continue;
     const uint64_t piece = bulk_piece(n);
     BulkPlan plan{};
-    if (bulk_plan(m->shapes[i], piece, bulk_kind(combine), true, &plan)) grouped += n;
+    if (bulk_plan(m->shapes[i], piece, bulk_kind(combine), total, &plan)) grouped += n;
     else plan = BulkPlan{};
     for (uint64_t at = 0; at < n; at += piece) {
       BulkJob j{};

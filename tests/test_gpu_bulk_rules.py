@@ -1,10 +1,14 @@
 """Which calls are grouped by bucket: the smallest share of a table's slots per design,
-bucket and kind of call; tables that never erase keep the plain call."""
+bucket and kind of call; tables that never erase keep the plain call where few
+operations share a key."""
 import ctypes
 
+import numpy as np
 import pytest
 
 import paper_2509_16407_amd as hw
+from paper_2509_16407_amd import workloads as w
+from gpu_util import dev, host, u8
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +41,39 @@ def test_tables_that_never_erase_keep_the_plain_call(design):
             assert (ts[0]._scratch(hw.OPS[op], n, c, None) is not None) == (flags == 0)
         m = hw.Multi(ts)
         assert (m._scratch((ctypes.c_uint64 * 3)(0, n, 2 * n), 2 * n, 0, None) is not None) == (flags == 0)
+
+
+def test_large_calls_on_tables_that_never_erase():
+    """From one operation per slot on: in groups of 2^17 operations, and alone in 2^24 slots."""
+    def alone(design, cap, n):
+        return hw.Table(cap, design, flags=hw.F_NO_ERASE)._scratch(hw.OPS["upsert"], n, 0, None) is not None
+
+    def group(design, tables, n):
+        m = hw.Multi([hw.Table(1 << 13, design, flags=hw.F_NO_ERASE) for _ in range(tables)])
+        return m._scratch((ctypes.c_uint64 * (tables + 1))(*[n * i for i in range(tables + 1)]), n * tables, 0, None) is not None
+    assert alone("DOUBLE_M", 1 << 24, 1 << 24) and not alone("DOUBLE_M", 1 << 24, (1 << 24) - 1)
+    assert not alone("DOUBLE_M", 1 << 23, 1 << 24) and not alone("CHAINING", 1 << 24, 1 << 25) and not alone("ICEBERG", 1 << 24, 1 << 25)
+    assert group("DOUBLE", 16, 1 << 13) and not group("DOUBLE", 15, 1 << 13) and not group("DOUBLE", 20, 8000)
+    assert group("CHAINING", 20, 12000) and not group("ICEBERG_M", 20, 12000)
+
+
+@pytest.mark.parametrize("design", ["DOUBLE", "DOUBLE_M", "CHAINING"])
+def test_group_of_tables_that_never_erase(design):
+    """Grouped SUM upserts, fresh and of present keys, beside a table with too few operations."""
+    n, u, tables = 20000, 9000, 8
+    ts = [hw.Table(1 << 14, design, flags=hw.F_NO_ERASE) for _ in range(tables)]
+    m = hw.Multi(ts)
+    pool = w.distinct_keys(w.stream_seed(330, hw.DESIGNS[design]), u * tables).reshape(tables, u)
+    pick = w.uniform_below(331, 0, n * tables, u).reshape(tables, n)
+    ns = [n] * (tables - 1) + [5000]
+    keys = np.concatenate([pool[i][pick[i][:c]] for i, c in enumerate(ns)])
+    offs = [0] + np.cumsum(ns).tolist()
+    assert m._scratch((ctypes.c_uint64 * len(offs))(*offs), len(keys), 0, None) is not None
+    for times in (1, 2):
+        st = u8(m.upsert(offs, dev(keys), dev(np.ones(len(keys), np.uint64))))
+        for i, t in enumerate(ts):
+            k, c = np.unique(keys[offs[i]: offs[i + 1]], return_counts=True)
+            assert (st[offs[i]: offs[i + 1]] == hw.ST_DONE).sum() == (len(k) if times == 1 else 0)
+            f, v = t.query(dev(k))
+            assert bool((f == hw.ST_DONE).all()) and np.array_equal(host(v), c.astype(np.uint64) * np.uint64(times))
+            assert t.size() == len(k)
