@@ -187,7 +187,11 @@ typedef struct {
                            find it held wait in a FIFO ticket queue, so a wait
                            is bounded by the operations queued ahead times one
                            critical section; an operation still waiting at the
-                           limit gives up with HWAVE_ST_TIMEOUT (see there)    */
+                           limit gives up with HWAVE_ST_TIMEOUT (see there).
+                           A call with scratch memory holds a bucket's lock while
+                           a block works on up to 1024 operations of its and
+                           its neighbours' (below a millisecond); tables whose limit
+                           is below 1 ms (iceberg: 4 ms) take only plain calls  */
 } hwave_config;
 
 /* Fills *out with the design's defaults: the bucket size and tile width of the

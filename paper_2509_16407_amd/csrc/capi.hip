@@ -452,10 +452,22 @@ struct BulkShape {
   uint32_t kv_bits, B;  // B: slot units per home bucket
   uint64_t nbh, backs;  // home buckets; iceberg's backyard buckets
   bool stable;          // the table never erases
+  bool impatient;       // its writers may not wait for a grouped part's locks
 };
+// A part's block holds the locks of its buckets while it works on all their operations, where a
+// plain writer holds one for one operation.  So tables whose lock_timeout_us is below what a part
+// takes keep the plain calls: iceberg's parts place backyard keys with few tiles (ICEBERG, 2^20 slots
+// from 0.75 to 0.95 beside small upserts: with 100 us, 744 timed out beside the grouped call, none
+// beside the plain one; with 200 none), others' are done in tens of microseconds (plain calls of that
+// size time out among themselves with 50).  The lines leave a factor of 20.
+constexpr uint32_t BULK_PATIENCE_US = 1000, BULK_PATIENCE_ICEBERG_US = 4000;
+
 BulkShape bulk_shape(const hwave_table* t) {
+  const bool iceberg = design_iceberg(t->design);
+  const uint64_t patience = (uint64_t)(iceberg ? BULK_PATIENCE_ICEBERG_US : BULK_PATIENCE_US) * 100;  // in ticks
   return BulkShape{t->ks, t->design, t->cfg.kv_bits, design_chain(t->design) ? 8u : t->cfg.bucket_slots,
-                   t->la.tv.nb_front, t->la.tv.nb_back, t->la.tv.no_erase != 0};
+                   t->la.tv.nb_front, t->la.tv.nb_back, t->la.tv.no_erase != 0,
+                   t->la.tv.lock_limit < patience};
 }
 
 // What a grouped call does: KEEP upserts are inserts, which mostly bring absent keys.
@@ -503,7 +515,7 @@ bool bulk_stable(const BulkShape& t, uint64_t n, uint64_t call) {
 bool bulk_plan(const BulkShape& t, uint64_t n, BulkKind kind, uint64_t call, BulkPlan* p) {
   const bool member = call != 0;
   const bool erase = kind == BULK_ERASE;
-  if (!(erase ? t.ks->bulk_erase : t.ks->bulk_upsert) || n < (member ? 1 : BULK_MIN_OPS) || n > BULK_CHUNK) return false;
+  if (!(erase ? t.ks->bulk_erase : t.ks->bulk_upsert) || n < (member ? 1 : BULK_MIN_OPS) || n > BULK_CHUNK || t.impatient) return false;
   const uint32_t B = t.B;
   const uint64_t nbh = t.nbh;
   if (!erase && t.stable && !bulk_stable(t, n, call)) return false;

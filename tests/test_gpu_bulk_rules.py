@@ -77,3 +77,17 @@ def test_group_of_tables_that_never_erase(design):
             f, v = t.query(dev(k))
             assert bool((f == hw.ST_DONE).all()) and np.array_equal(host(v), c.astype(np.uint64) * np.uint64(times))
             assert t.size() == len(k)
+
+
+@pytest.mark.parametrize("design,least_us", [("DOUBLE", 1000), ("P2_M", 1000), ("CHAINING", 1000), ("ICEBERG", 4000), ("ICEBERG_M", 4000)])
+def test_tables_with_little_patience_keep_the_plain_calls(design, least_us):
+    """Their writers would time out beside a block that holds a bucket's lock for a part."""
+    cap, n = 1 << 16, 60000
+    for us in (0, least_us, least_us - 1, 10):
+        ts = [hw.Table(cap, design, lock_timeout_us=us) for _ in range(2)]
+        patient = us in (0, least_us)
+        assert (ts[0]._scratch(hw.OPS["erase"], n, 0, None) is not None) == patient
+        if design != "P2_M":
+            assert (ts[0]._scratch(hw.OPS["upsert"], n, 0, None) is not None) == patient
+            m = hw.Multi(ts)
+            assert (m._scratch((ctypes.c_uint64 * 3)(0, n, 2 * n), 2 * n, 0, None) is not None) == patient
