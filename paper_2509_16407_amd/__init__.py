@@ -192,9 +192,11 @@ def _stream(stream):
 
 def _scratch_memory(n, device, stream):
     """n bytes from torch's allocator on the given stream; None without room for them,
-    while the stream is being captured into a graph, or if it is another device's."""
+    while the stream is being captured into a graph, or if it is another device's or
+    an object that does not say whose it is."""
     import torch
-    if (torch.cuda.current_device() if stream is None else stream.device.index) != device.index:
+    on = torch.cuda.current_device() if stream is None else getattr(getattr(stream, "device", None), "index", None)
+    if on != device.index:
         return None  # the call runs on another device's stream than the memory would belong to
     if stream is not None:
         with torch.cuda.stream(torch.cuda.ExternalStream(stream.cuda_stream, device=device)):
