@@ -437,8 +437,8 @@ int hwave_multi_upsert_scratch(hwave_multi* m, const uint64_t* h_offsets, const 
  * search, Section 5): times every multi-table menu configuration whose design
  * bit is set in design_mask (1 << hwave_design) for tables of `capacity` slots,
  * on a synthetic group-by SUM-upsert batch that fills them to `load`, spread
- * over enough tables of that class to fill the GPU and run through the
- * persistent multi-table kernel.  `flags` are the tables' HWAVE_F_* flags.
+ * over enough tables of that class to fill the GPU and run as one group call with
+ * scratch memory (hwave_multi_upsert_scratch).  `flags` are the tables' HWAVE_F_* flags.
  * Writes up to results_cap timings to `results` (their count to *n_results) and
  * the fastest to *best.  A configuration that cannot hold the load -- any
  * operation of its batch ended FULL -- is reported with its FULL count and is

@@ -1,8 +1,9 @@
 // Autotuner: picks a table configuration (design, bucket size, tile width) for a
 // capacity class by timing every candidate of the multi-table menu on the work
 // it will run -- a group-by SUM upsert batch that fills tables of that class to
-// the requested load, spread over enough tables of the class to fill the GPU,
-// through the persistent multi-table kernel.  The paper tunes bucket and tile
+// the requested load, spread over enough tables of the class to fill the GPU, in one
+// group call with scratch memory: grouped by bucket where that call is, through the
+// persistent multi-table kernel elsewhere.  The paper tunes bucket and tile
 // size by exhaustive search per design (Section 5); this does the same per
 // capacity class, at run time.
 #include <hip/hip_runtime.h>
@@ -145,6 +146,11 @@ int hwave_autotune(uint32_t kv_bits, uint64_t capacity, uint32_t design_mask, do
     if (rc == HWAVE_OK) rc = hwave_multi_create(&m, tabs.data(), n_tab, stream);
     std::vector<uint64_t> offs(n_tab + 1);
     for (uint32_t t = 0; t <= n_tab; t++) offs[t] = (uint64_t)t * 2 * D;
+    // the scratch memory a caller would give; without room for it the plain call is timed
+    uint8_t* scratch = nullptr;
+    uint64_t scratch_bytes = 0;
+    if (rc == HWAVE_OK) rc = hwave_multi_scratch(m, offs.data(), HWAVE_SUM, &scratch_bytes);
+    if (rc == HWAVE_OK && scratch_bytes && hipMalloc(&scratch, scratch_bytes) != hipSuccess) scratch = nullptr;
     float total_ms = 0.f;
     if (rc == HWAVE_OK) {
       if (kv_bits == 64)
@@ -160,7 +166,8 @@ int hwave_autotune(uint32_t kv_bits, uint64_t capacity, uint32_t design_mask, do
         rc = hwave_multi_clear(m, stream);
         if (rc) break;
         (void)hipEventRecord(a, s);
-        rc = hwave_multi_upsert(m, offs.data(), keys, vals, HWAVE_SUM, status, stream);
+        rc = hwave_multi_upsert_scratch(m, offs.data(), keys, vals, HWAVE_SUM, status, scratch,
+                                        scratch ? scratch_bytes : 0, stream);
         (void)hipEventRecord(b, s);
         if (hipEventSynchronize(b) != hipSuccess) rc = HWAVE_EDEVICE;
         float ms = 0.f;
@@ -182,6 +189,7 @@ int hwave_autotune(uint32_t kv_bits, uint64_t capacity, uint32_t design_mask, do
     if (m) hwave_multi_destroy(m);
     for (auto* t : tabs)
       if (t) hwave_destroy(t);
+    if (scratch) (void)hipFree(scratch);
     (void)hipFree(region);
     (void)hipFree(keys);
     (void)hipFree(vals);
