@@ -21,6 +21,7 @@ Prints ONE JSON line (see the `result` dict at the end).
 from __future__ import annotations
 
 import argparse
+import contextlib
 import hashlib
 import json
 import os
@@ -46,7 +47,7 @@ ALGO_BYTES = {
 }
 
 SOURCES_FOR_TRAFFIC = ["paper_2509_16407_amd/csrc/hw_device.hpp", "paper_2509_16407_amd/csrc/hw_ops.hpp",
-                       "paper_2509_16407_amd/csrc/hw_launch.hpp"]
+                       "paper_2509_16407_amd/csrc/hw_launch.hpp", "paper_2509_16407_amd/csrc/hw_bulk.hpp"]
 
 
 def kernel_source_hash() -> str:
@@ -290,6 +291,38 @@ def verify_step(step: Step, d) -> int:
     return n_full
 
 
+@contextlib.contextmanager
+def ungrouped():
+    """Bulk writes run as plain calls, one tile per operation, not grouped by bucket."""
+    import paper_2509_16407_amd as hw
+    saved = hw.Table._scratch, hw.Multi._scratch
+    hw.Table._scratch = hw.Multi._scratch = lambda *a: None
+    try:
+        yield
+    finally:
+        hw.Table._scratch, hw.Multi._scratch = saved
+
+
+def plain_insert_gops(step: Step, reps=2) -> dict:
+    """Rates of the three load phases as plain calls: what the phased variant, which has no
+    grouped form, is compared with."""
+    import torch
+    ev = {}
+    b = (0,) + tuple(step.bounds)
+    with ungrouped():
+        for r in range(reps + 1):
+            step.t.clear()
+            for name, lo, hi in zip(("insert_0.5", "insert_0.75", "insert_0.9"), b, b[1:]):
+                x, y = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                x.record()
+                step.t.insert(step.keys[lo:hi], step.vals[lo:hi], status=step.st[:hi - lo])
+                y.record()
+                if r:
+                    ev.setdefault(name, []).append((x, y))
+    torch.cuda.synchronize()
+    return {n: round(step.ops[n] / float(np.mean([x.elapsed_time(y) for x, y in v])) / 1e6, 3) for n, v in ev.items()}
+
+
 def bench_phased(step: Step, d, design: str, conc_rates: dict, reps=3):
     """Cost of concurrency (Section 6.4): the load phases and the query sets on the
     phased variant of `design` (no locks, plain cacheable loads in queries; chaining
@@ -381,9 +414,10 @@ def bench_designs(step: Step, d, designs, steps=2, warmup=1, verify=True):
             rates["mixed"] = round(step.mixed_ops / len(step.mixed) / ph["mixed"] / 1e6, 3)
         out[des] = {"bucket": step.t.bucket_slots, "tile": step.t.tile, "verified": bool(verify),
                     "step_gops": round(step.ops_per_step() * steps / wall / 1e9, 4), "phase_gops": rates}
+        plain = plain_insert_gops(step)
         step.t = None
         torch.cuda.empty_cache()
-        out[des]["phased"] = bench_phased(step, d, des, rates)
+        out[des]["phased"] = bench_phased(step, d, des, dict(rates, **plain))
         log("design %s: %.2f Gops/s per step (insert_0.9 %.2f, query+ %.2f, query- %.2f)"
             % (des, out[des]["step_gops"], rates["insert_0.9"], rates["query_pos"], rates["query_neg"]))
     step.t = main_t
@@ -724,11 +758,12 @@ def one_config(alls, ops_of):
 def bench_batched(n_tables=4096, e_min=10, e_max=22, load=0.85, reps=3, tune_reps=2, n_verify=16):
     """The batched form: n_tables uint32 tables with capacities 2^e,
     e uniform in [e_min, e_max], each receiving a group-by SUM-upsert batch that
-    fills it to `load`.  Times one persistent multi-table launch (configuration
-    autotuned per capacity class) against one plain launch per table (same
-    configurations) and against one persistent launch with a fixed default
-    configuration.  A group of one configuration runs on that configuration's own
-    kernel, a group of several on the menu's; so when the classes chose different
+    fills it to `load`.  Times one call over all tables (configuration
+    autotuned per capacity class) against one plain launch per table and one call per
+    table (same configurations; the calls group by bucket where that pays) and against one
+    persistent launch with a fixed default configuration.  A group of one configuration
+    runs grouped by bucket, in a few launches over all tables, a group of several on the
+    menu's persistent kernel; so when the classes chose different
     configurations, one launch with the single configuration of least estimated
     time (from the tuner's rates) is timed too, and the faster group is the
     batched result.  Verifies every table's size and, on a sample of tables, every
@@ -803,11 +838,13 @@ def bench_batched(n_tables=4096, e_min=10, e_max=22, load=0.85, reps=3, tune_rep
             for i, t in enumerate(tabs):
                 a, b = int(offsets[i]), int(offsets[i + 1])
                 t.upsert(kd[a:b], vd[a:b], status=st[a:b])
-        ms_p = timed(plain, m.clear)
+        ms_c = timed(plain, m.clear)
+        with ungrouped():
+            ms_p = timed(plain, m.clear)
         verify(tabs)  # the plain run's
         del m, tabs
         torch.cuda.empty_cache()
-        return ms_b, ms_p
+        return ms_b, ms_p, ms_c
 
     ops_of = {e: int(sum(offsets[i + 1] - offsets[i] for i in range(n_tables) if exps[i] == e)) for e in classes}
     one_cfg = lambda alls: one_config(alls, ops_of)
@@ -831,11 +868,11 @@ def bench_batched(n_tables=4096, e_min=10, e_max=22, load=0.85, reps=3, tune_rep
         torch.cuda.empty_cache()
         return c, ms
 
-    ms_batched, ms_plain = batched_and_plain(tuned, 0)
+    ms_batched, ms_plain, ms_calls = batched_and_plain(tuned, 0)
     uni = uniform_group(tuned, rejected, 0)
     log("batched: verified sizes of all tables and %d tables against their group-by sums" % len(pick))
     # group-by tables never erase: declared so, a repeated key is summed without its lock
-    ms_batched_ne, ms_plain_ne = batched_and_plain(tuned_ne, hw.F_NO_ERASE)
+    ms_batched_ne, ms_plain_ne, ms_calls_ne = batched_and_plain(tuned_ne, hw.F_NO_ERASE)
     uni_ne = uniform_group(tuned_ne, alls_ne, hw.F_NO_ERASE)
     log("batched: erase-free tables %.2f Gops/s in one launch (per-class configurations) vs %.2f Gops/s plain "
         "(verified)"
@@ -865,12 +902,14 @@ def bench_batched(n_tables=4096, e_min=10, e_max=22, load=0.85, reps=3, tune_rep
             "batched_ms": round(ms_best, 3), "batched_gops": gops(ms_best), "group": policy,
             "per_class_ms": round(ms_batched, 3), "per_class_gops": gops(ms_batched),
             "plain_ms": round(ms_plain, 3), "plain_gops": gops(ms_plain),
+            "call_per_table_ms": round(ms_calls, 3), "call_per_table_gops": gops(ms_calls),
             "default_cfg_batched_ms": round(ms_default, 3), "default_cfg_batched_gops": gops(ms_default),
             "speedup_vs_plain": round(ms_plain / ms_best, 3),
             "per_class_kernel": kernel_of(tuned), "one_config": one(uni),
             "erase_free": {"batched_ms": round(ms_best_ne, 3), "batched_gops": gops(ms_best_ne), "group": policy_ne,
                            "per_class_ms": round(ms_batched_ne, 3), "per_class_gops": gops(ms_batched_ne),
                            "plain_ms": round(ms_plain_ne, 3), "plain_gops": gops(ms_plain_ne),
+                           "call_per_table_ms": round(ms_calls_ne, 3), "call_per_table_gops": gops(ms_calls_ne),
                            "per_class_kernel": kernel_of(tuned_ne), "one_config": one(uni_ne),
                            "tuning": {str(e): "%s/b%d/t%d %.2f" % (v["design"], v["bucket"], v["tile"], v["gops"])
                                       for e, v in tuned_ne.items()}},
@@ -1096,6 +1135,19 @@ KERNEL_OF = {"insert_0.5": "k_upsert", "insert_0.75": "k_upsert", "insert_0.9": 
              "mixed": "k_mixed"}
 
 
+def kernels_of(step: Step) -> dict:
+    """Phase -> what it runs: KERNEL_OF, or grouped_<kind> where the call is grouped by
+    bucket (k_bulk_zero, k_bulk_split, k_bulk_write, k_bulk_back and k_bulk_finish)."""
+    import paper_2509_16407_amd as hw
+    res = dict(KERNEL_OF)
+    for phase in step.phase_names:
+        op = phase.split("_")[0]
+        if op in ("insert", "upsert", "erase") and \
+                step.t._scratch(hw.OPS[op], step.ops[phase], hw.COMBINES["keep" if op == "insert" else "sum"], None) is not None:
+            res[phase] = "grouped_" + op
+    return res
+
+
 def algo_kind(phase: str) -> str:
     return "insert" if phase.startswith("insert") else phase
 
@@ -1144,13 +1196,13 @@ def load_requests():
     return phases, float(rec["reference_greq_s"])
 
 
-def roofline(phase_ms: dict, per_step_ops: dict, steps: int, traffic_by_phase):
+def roofline(phase_ms: dict, per_step_ops: dict, steps: int, traffic_by_phase, kernel_of=KERNEL_OF):
     """Roofline object of the dominant kernel (largest total time per step):
     algorithmic bytes of all its launches in a step / their total time, against the
     8 TB/s HBM peak; `traffic` = measured HBM bytes per launch (or None)."""
     kern_ms, kern_bytes, kern_launch, kern_meas = {}, {}, {}, {}
     for ph, lst in phase_ms.items():
-        k = KERNEL_OF[ph]
+        k = kernel_of[ph]
         kern_ms[k] = kern_ms.get(k, 0.0) + float(np.sum(lst)) / steps
         n_launch = len(lst) // steps
         kern_launch[k] = kern_launch.get(k, 0) + n_launch
@@ -1176,7 +1228,7 @@ def roofline(phase_ms: dict, per_step_ops: dict, steps: int, traffic_by_phase):
         # random single-line accesses: the request rate, not the byte rate, is the ceiling
         by_phase, ref = req
         n_req = sum(by_phase[ph] * (len(lst) // steps) for ph, lst in phase_ms.items()
-                    if KERNEL_OF[ph] == dom and ph in by_phase)
+                    if kernel_of[ph] == dom and ph in by_phase)
         per_launch = n_req / kern_launch[dom]
         g = per_launch / (avg_launch_ms * 1e-3) / 1e9
         roof["fabric_requests"] = {"per_launch": round(per_launch), "achieved_Greq_s": round(g, 2),
@@ -1275,7 +1327,7 @@ def main():
     per_step_ops = dict(step.ops)
     if step.mixed:
         per_step_ops["mixed"] = step.mixed_ops // len(step.mixed)
-    roof = roofline(phase_ms, per_step_ops, args.steps, load_traffic())
+    roof = roofline(phase_ms, per_step_ops, args.steps, load_traffic(), kernels_of(step))
     rates["upsert_miss_0.9"] = upsert_miss(step)
     log("upsert misses 0.75 -> 0.9: %.2f Gops/s" % rates["upsert_miss_0.9"]["gops"])
     probes = None
@@ -1300,9 +1352,10 @@ def main():
         main_t = step.t
         designs[args.design] = {"bucket": step.t.bucket_slots, "tile": step.t.tile, "main": True,
                                 "phase_gops": {k: v["gops"] for k, v in rates.items()}}
+        plain = plain_insert_gops(step)
         step.t = None
         torch.cuda.empty_cache()
-        designs[args.design]["phased"] = bench_phased(step, d, args.design, designs[args.design]["phase_gops"])
+        designs[args.design]["phased"] = bench_phased(step, d, args.design, dict(designs[args.design]["phase_gops"], **plain))
         step.t = main_t
 
     zipf = None
