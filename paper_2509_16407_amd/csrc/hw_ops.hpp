@@ -929,7 +929,7 @@ struct Ops {
   // lock held by one other tile is usually free again within a critical
   // section).  Then it takes a ticket of the bucket's lock queue, looks at the
   // serving counter at times spaced by its place in the queue, and once at the
-  // head tries the byte until it takes it, then passes the queue on.  LOOK: after
+  // head tries the byte until it takes it, then passes the queue on.  LOOK and `look`: after
   // LOCK_SPINS retries look_up() may settle the operation without the lock
   // (ST_EXISTED), and again after as many more, before the ticket.
   //
@@ -940,7 +940,8 @@ struct Ops {
   // round trips (the retries, the most common wait, come last in the round),
   // and tiles of one wave that wait on each other cannot deadlock.
   template <bool LOOK, class G, class F>
-  __device__ static uint8_t locked(const TableDev& tv, const Tile<T>& tile, uint32_t b, G&& look_up, F&& cs) {
+  __device__ static uint8_t locked(const TableDev& tv, const Tile<T>& tile, uint32_t b, bool look, G&& look_up,
+                                F&& cs) {
     uint32_t* const ws = wait_state();
     enum : uint32_t { HAVE = 0, RETRY = 1, QUEUED = 2, HEAD = 3, DONE = 4 };
     uint32_t stage = try_lock(tv.locks, b, tile) ? HAVE : RETRY;
@@ -990,10 +991,10 @@ struct Ops {
         for (uint32_t i = 0; i < (1u << pause); ++i) __builtin_amdgcn_s_sleep(2);
         if (lock_looks_free(tv.locks, b, tile) && try_lock(tv.locks, b, tile)) {
           stage = HAVE;
-        } else if (LOOK && (retries + 1) % LOCK_SPINS == 0 && look_up()) {
+        } else if (LOOK && look && (retries + 1) % LOCK_SPINS == 0 && look_up()) {
           status = ST_EXISTED;
           stage = DONE;
-        } else if (retries + 1 == (LOOK ? 2 * LOCK_SPINS : LOCK_SPINS)) {
+        } else if (retries + 1 == (LOOK && look ? 2 * LOCK_SPINS : LOCK_SPINS)) {
           const uint64_t w = take_ticket(tv.lockq, b & tv.lockq_mask, tile);
           const uint32_t mine = (uint32_t)(w >> 32), since = now_ticks();
           stage = (uint32_t)w == mine ? HEAD : QUEUED;
@@ -1078,7 +1079,7 @@ struct Ops {
       return true;
     };
     if (!erase && tv.no_erase && look_up()) return ST_EXISTED;
-    return locked<LOOK>(tv, tile, h.b1, [&]() -> bool { return tv.no_erase && look_up(); }, [&]() -> uint8_t {
+    return locked<LOOK>(tv, tile, h.b1, LOOK && tv.no_erase, look_up, [&]() -> uint8_t {
       if (erase) return erase_locked(tv, tile, h, key, tag);
       return upsert_locked<false>(tv, tile, h, key, val, tag, combine);
     });
