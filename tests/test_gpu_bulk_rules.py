@@ -91,3 +91,10 @@ def test_tables_with_little_patience_keep_the_plain_calls(design, least_us):
             assert (ts[0]._scratch(hw.OPS["upsert"], n, 0, None) is not None) == patient
             m = hw.Multi(ts)
             assert (m._scratch((ctypes.c_uint64 * 3)(0, n, 2 * n), 2 * n, 0, None) is not None) == patient
+
+
+def test_groups_of_tables_with_few_operations_each():
+    """A block per table pays from 64 operations on."""
+    m = hw.Multi([hw.Table(1 << 8, "DOUBLE_M") for _ in range(100)])
+    grouped = lambda n: m._scratch((ctypes.c_uint64 * 101)(*[n * i for i in range(101)]), 100 * n, 0, None) is not None
+    assert grouped(64) and not grouped(63)
