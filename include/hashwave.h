@@ -297,7 +297,7 @@ int hwave_mixed_noalloc(hwave_table* t, const uint8_t* d_ops, const void* d_keys
 int hwave_size(hwave_table* t, uint64_t* d_count, void* stream);
 
 /* Copies every live (key, value) pair to d_keys/d_vals (capacity elements
- * each, in slot order) and their number to *d_count.  Meant for a quiescent
+ * each, in no order) and their number to *d_count.  Meant for a quiescent
  * table (checkpoint dump, tests).  Not a paper operation: the dump that the
  * verification compares with the oracle's map. */
 int hwave_export(hwave_table* t, void* d_keys, void* d_vals, uint64_t* d_count, void* stream);

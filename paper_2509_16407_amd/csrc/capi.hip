@@ -440,9 +440,9 @@ constexpr uint64_t BULK_CHUNK = HW_BULK_CHUNK;
 constexpr uint64_t BULK_RESIDENT = 1536;
 constexpr uint32_t BULK_FILL = 512;
 
-// Fewest operations of a group's table that are grouped: a block's chain of round trips is the same for
-// fewer (400 tables of 2^8 slots, DOUBLE_M, 33 operations each: 87 us plain, 106 grouped; 64
-// each: 106 / 101).
+// Fewest operations of a group's table that are grouped: a block's chain of round trips is
+// the same for fewer (400 tables of 2^8 slots, DOUBLE_M, present keys: 33 operations each
+// 87 us plain, 106 grouped; 51 104 / 110; 64 123 / 96).
 constexpr uint64_t BULK_MIN_MEMBER = 64;
 
 // Room for a bin that receives `mean` operations on average: seven standard
@@ -490,8 +490,8 @@ BulkKind bulk_kind(int combine) { return combine == HWAVE_KEEP ? BULK_INSERT : B
 //   32-bit keys:         8 slots 0.16: present 25 / 30 (2^15); 0.21: 30 / 29.  16 and more 0.16: 31 / 29
 //   64-bit, no tags:     DOUBLE 0.25: inserts to 0.95 69 / 84 (2^16), present 25 / 30 (2^14), but 2^13
 //                        fresh 32 / 27; 0.29: 73 / 73, 28 / 29.  Erases 0.25: absent 30 / 41, 0.29
-//                        present 30 / 34 (2^13); 0.33 35 / 35.  ICEBERG inserts to 0.97, 0.12 of the slots: 216 / 255
-//                        (2^21); upserts of present keys 115 / 43 (0.21, 2^19)
+//                        present 30 / 34 (2^13); 0.33 35 / 35.  ICEBERG inserts to 0.97, 0.12 of
+//                        the slots: 216 / 255 (2^21); upserts of present keys 115 / 43 (0.21, 2^19)
 //   chaining:            erases of absent keys 0.29: 20 / 26 (2^14), 0.37: 24 / 25; upserts walk whole
 //                        chains under the lock with one tile: 0.69: 83 / 74 (2^19), inserts to 0.95 86 / 83
 uint64_t bulk_min_percent(const BulkShape& t, BulkKind kind) {
@@ -503,12 +503,13 @@ uint64_t bulk_min_percent(const BulkShape& t, BulkKind kind) {
   return kind == BULK_INSERT && t.nbh * t.B <= 1u << 13 ? 25 : 29;
 }
 
-// Whether an upsert of a table that never erases is grouped.  Its plain upserts of present keys
-// take no lock: one look and one atomic, which grouping beats only where several operations
-// meet in a key, and where memory or a launch's many tables bound the plain call.  Plain against grouped, microseconds, present
-// keys unless noted: DOUBLE_M 0.2 operations per slot 11 / 30 (2^15), 421 / 576 (2^25); 1.7 per slot 31 / 43 (2^18), 339 / 367
-// (2^22), 1478 / 1507 (2^24; fresh 2863 / 1619); CHAINING 1451 / 1720 (2^24).  Groups with 1.7 per
-// slot: 400 tables of 2^12 slots 294 / 195 (fresh 851 / 203), 40 of 2^10 48 / 50; ICEBERG_M 56 / 77.
+// Whether an upsert of a table that never erases is grouped.  Its plain upserts of present
+// keys take no lock: one look and one atomic, which grouping beats only where several
+// operations meet in a key, and where memory or a launch's many tables bound the plain call.
+// Plain against grouped, microseconds, present keys unless noted: DOUBLE_M 0.2 operations per
+// slot 11 / 30 (2^15), 421 / 576 (2^25); 1.7 per slot 31 / 43 (2^18), 339 / 367 (2^22), 1478 / 1507
+// (2^24; fresh 2863 / 1619); CHAINING 1451 / 1720 (2^24).  Groups with 1.7 per slot: 400
+// tables of 2^12 slots 294 / 195 (fresh 851 / 203), 40 of 2^10 48 / 50; ICEBERG_M 56 / 77.
 bool bulk_stable(const BulkShape& t, uint64_t n, uint64_t call) {
   if (n < t.nbh * t.B || design_iceberg(t.design)) return false;
   return call ? call >= 1u << 17 : !design_chain(t.design) && t.nbh * t.B >= 1u << 24;
@@ -520,7 +521,8 @@ bool bulk_stable(const BulkShape& t, uint64_t n, uint64_t call) {
 bool bulk_plan(const BulkShape& t, uint64_t n, BulkKind kind, uint64_t call, BulkPlan* p) {
   const bool member = call != 0;
   const bool erase = kind == BULK_ERASE;
-  if (!(erase ? t.ks->bulk_erase : t.ks->bulk_upsert) || n < (member ? BULK_MIN_MEMBER : BULK_MIN_OPS) || n > BULK_CHUNK || t.impatient) return false;
+  if (!(erase ? t.ks->bulk_erase : t.ks->bulk_upsert) || t.impatient) return false;
+  if (n < (member ? BULK_MIN_MEMBER : BULK_MIN_OPS) || n > BULK_CHUNK) return false;
   const uint32_t B = t.B;
   const uint64_t nbh = t.nbh;
   if (!erase && t.stable && !bulk_stable(t, n, call)) return false;
@@ -602,7 +604,9 @@ bool bulk_run(hwave_table* t, bool erase, const void* keys, const void* vals, ui
               void* scratch, uint64_t scratch_bytes, hipStream_t s, hipError_t* err) {
   BulkPlan p;
   const uint64_t piece = bulk_piece(n), w = t->cfg.kv_bits / 8;
-  if (!scratch || ((uintptr_t)scratch % ALIGN) || !bulk_plan(bulk_shape(t), piece, erase ? BULK_ERASE : bulk_kind(combine), 0, &p) || p.bytes > scratch_bytes) return false;
+  if (!scratch || ((uintptr_t)scratch % ALIGN) ||
+      !bulk_plan(bulk_shape(t), piece, erase ? BULK_ERASE : bulk_kind(combine), 0, &p) || p.bytes > scratch_bytes)
+    return false;
   *err = hipSuccess;
   for (uint64_t at = 0; at < n && *err == hipSuccess; at += piece) {
     const uint64_t m = n - at < piece ? n - at : piece;

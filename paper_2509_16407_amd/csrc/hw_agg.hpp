@@ -108,8 +108,8 @@ __device__ void agg_window(const TableDev& tv, AggLds<typename C::K>& L, const t
   wave_sync();
   const Tile<C::T> tile;
   // Waves start at different places of their lists: the entries are in hash order, and
-  // from the front every wave would come to a hot key's bucket at the same time (4 M operations on 1.6 M Zipf
-  // keys: 1.80 ms, 1.28 with this).
+  // from the front every wave would come to a hot key's bucket at the same time (4 M
+  // operations on 1.6 M Zipf keys: 1.80 ms, 1.28 with this).
   const uint32_t first = (uint32_t)(((uint64_t)(uint32_t)(i0 / AGG_WIN * 0x9E3779B1u) * n_u) >> 32);
   for (uint32_t u = lane / C::T; u < n_u; u += 64 / C::T) {
     const uint32_t e = L.list[u + first < n_u ? u + first : u + first - n_u];

@@ -19,7 +19,7 @@
 //  3. k_bulk_finish brings the statuses back to the operations' order (k_bulk_back
 //     before it, for the second level) and runs what the parts did not take -- bins
 //     that overflowed (skewed keys), buckets whose lock another call held -- one tile
-//     each, like a plain launch.
+//     per distinct key of 64 operations.
 //
 // Locks: a block tries each lock byte once and never waits for one, so it cannot
 // deadlock with tiles that wait in the queues; it holds them for a bounded time.
