@@ -929,9 +929,9 @@ struct Ops {
   // lock held by one other tile is usually free again within a critical
   // section).  Then it takes a ticket of the bucket's lock queue, looks at the
   // serving counter at times spaced by its place in the queue, and once at the
-  // head tries the byte until it takes it, then passes the queue on.  LOOK and `look`: after
-  // LOCK_SPINS retries look_up() may settle the operation without the lock
-  // (ST_EXISTED), and again after as many more, before the ticket.
+  // head tries the byte until it takes it, then passes the queue on.  LOOK and look > 0: at
+  // every `look`th retry look_up() may settle the operation without the lock
+  // (ST_EXISTED); look = 1 retries twice as often.
   //
   // Lanes of a wave run in lockstep, so every tile of the wave goes round this
   // loop until the last one is done.  The critical section comes first in each
@@ -940,7 +940,7 @@ struct Ops {
   // round trips (the retries, the most common wait, come last in the round),
   // and tiles of one wave that wait on each other cannot deadlock.
   template <bool LOOK, class G, class F>
-  __device__ static uint8_t locked(const TableDev& tv, const Tile<T>& tile, uint32_t b, bool look, G&& look_up,
+  __device__ static uint8_t locked(const TableDev& tv, const Tile<T>& tile, uint32_t b, uint32_t look, G&& look_up,
                                 F&& cs) {
     uint32_t* const ws = wait_state();
     enum : uint32_t { HAVE = 0, RETRY = 1, QUEUED = 2, HEAD = 3, DONE = 4 };
@@ -989,12 +989,12 @@ struct Ops {
         // then a look at the byte and the OR if it reads clear
         const uint32_t retries = ws[3], pause = LOOK && retries >= LOCK_SPINS ? LOCK_SPINS - 1 : retries;
         for (uint32_t i = 0; i < (1u << pause); ++i) __builtin_amdgcn_s_sleep(2);
-        if (lock_looks_free(tv.locks, b, tile) && try_lock(tv.locks, b, tile)) {
-          stage = HAVE;
-        } else if (LOOK && look && (retries + 1) % LOCK_SPINS == 0 && look_up()) {
+        if (LOOK && look && (retries + 1) % look == 0 && look_up()) {
           status = ST_EXISTED;
           stage = DONE;
-        } else if (retries + 1 == (LOOK && look ? 2 * LOCK_SPINS : LOCK_SPINS)) {
+        } else if (lock_looks_free(tv.locks, b, tile) && try_lock(tv.locks, b, tile)) {
+          stage = HAVE;
+        } else if (retries + 1 == (LOOK && look == 1 ? 2 * LOCK_SPINS : LOCK_SPINS)) {
           const uint64_t w = take_ticket(tv.lockq, b & tv.lockq_mask, tile);
           const uint32_t mine = (uint32_t)(w >> 32), since = now_ticks();
           stage = (uint32_t)w == mine ? HEAD : QUEUED;
@@ -1027,25 +1027,25 @@ struct Ops {
   // SUM/MIN/MAX combine of a present key goes to row hot_row of the accumulators
   // instead of the value word.
   //
-  // LOOK (windows of merged operations): a tile whose retries found the lock held
-  // looks for its key again before it joins the lock's queue.  At the start of a
-  // skewed batch every window holds the same few absent keys; once the first of
-  // them has inserted a key, the others need no lock, where each would wait in line
-  // for it (1.5 M Zipf operations on a fresh P2HT(M) of 2^21 slots: 7.7 ms without,
-  // 0.54 with it; as many distinct keys 0.450 and 0.456, 0.525 with a look before every
-  // retry).
+  // LOOK (windows of merged operations): a tile that finds the lock held looks for
+  // its key again, at every `look`th retry.  At the start of a skewed batch every
+  // window holds the same few absent keys; once the first of them has inserted a key, the
+  // others need no lock, where each would wait in line for it.  Windows with many
+  // duplicates (agg_window) look at every retry, others once before the ticket: 1.5 M
+  // Zipf operations on a fresh P2HT(M) of 2^21 slots take 7.7 ms without looks, 0.52 so, 0.55
+  // with one look each; as many distinct keys 0.450, 0.447 so, 0.525 with a look at every retry.
   template <bool LOOK = false>
   __device__ static __forceinline__ uint8_t upsert(const TableDev& tv, const Tile<T>& tile, K key, K val,
-                                   int combine, int hot_row = -1) {
-    return write<LOOK>(tv, tile, key, val, combine, false, hot_row);
+                                                   int combine, int hot_row = -1, uint32_t look = 0) {
+    return write<LOOK>(tv, tile, key, val, combine, false, hot_row, look);
   }
 
   // Upsert (erase false) or erase (erase true) of one key: the write path both
   // share.  Callers pass a constant `erase`, so the other kind's code folds
   // away.
   template <bool LOOK = false>
-  __device__ static __forceinline__ uint8_t write(const TableDev& tv, const Tile<T>& tile, K key, K val, int combine, bool erase,
-                                  int hot_row = -1) {
+  __device__ static __forceinline__ uint8_t write(const TableDev& tv, const Tile<T>& tile, K key, K val, int combine,
+                                                  bool erase, int hot_row = -1, uint32_t look = 0) {
     if (key >= Keys<K>::FIRST_INVALID || (erase && tv.no_erase)) return ST_INVALID;
     if constexpr (C::CUCKOO) {
       K unused;
@@ -1079,7 +1079,7 @@ struct Ops {
       return true;
     };
     if (!erase && tv.no_erase && look_up()) return ST_EXISTED;
-    return locked<LOOK>(tv, tile, h.b1, LOOK && tv.no_erase, look_up, [&]() -> uint8_t {
+    return locked<LOOK>(tv, tile, h.b1, tv.no_erase ? look : 0u, look_up, [&]() -> uint8_t {
       if (erase) return erase_locked(tv, tile, h, key, tag);
       return upsert_locked<false>(tv, tile, h, key, val, tag, combine);
     });
