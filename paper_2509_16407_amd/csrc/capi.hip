@@ -483,22 +483,22 @@ BulkKind bulk_kind(int combine) { return combine == HWAVE_KEEP ? BULK_INSERT : B
 // kind of such a call (into an empty table, to loads of 0.85 and 0.95, of present keys;
 // erases of present and of absent keys) is within 5% of the plain call or faster, in tables of 2^12
 // to 2^25 slots.  Plain against grouped, microseconds, below the line and at it:
-//   tags, 32 slots:      inserts and upserts 0.10: 36 / 30 (2^15), 317 / 308 (2^25, present keys);
-//                        ICEBERG_M to 0.95, 0.10 to 0.12: 89 / 104 (2^18), 99 / 91 (2^17)
+//   tags, 32 slots:      inserts and upserts 0.10: 36 / 30 (2^15), 317 / 308 (2^25, present keys)
 //   tags, 16 slots:      0.10: DOUBLE_M present 27 / 30 (2^15), P2HT(M) erases of absent keys 21 / 23;
 //                        0.13: 32 / 29, 24 / 23
 //   32-bit keys:         8 slots 0.16: present 25 / 30 (2^15); 0.21: 30 / 29.  16 and more 0.16: 31 / 29
-//   64-bit, no tags:     DOUBLE 0.25: inserts to 0.95 69 / 84 (2^16), present 25 / 30 (2^14), but 2^13
+//   64-bit, no tags:     8 slots 0.25: inserts to 0.95 69 / 84 (2^16), present 25 / 30 (2^14), but 2^13
 //                        fresh 32 / 27; 0.29: 73 / 73, 28 / 29.  Erases 0.25: absent 30 / 41, 0.29
-//                        present 30 / 34 (2^13); 0.33 35 / 35.  ICEBERG inserts to 0.97, 0.12 of
-//                        the slots: 216 / 255 (2^21); upserts of present keys 115 / 43 (0.21, 2^19)
+//                        present 30 / 34 (2^13); 0.33 35 / 35.  16 and more 0.25: P2HT erases 96 / 89 (2^21).
+//                        ICEBERG 0.21: upserts of present keys 115 / 43 (2^19)
 //   chaining:            erases of absent keys 0.29: 20 / 26 (2^14), 0.37: 24 / 25; upserts walk whole
 //                        chains under the lock with one tile: 0.69: 83 / 74 (2^19), inserts to 0.95 86 / 83
 uint64_t bulk_min_percent(const BulkShape& t, BulkKind kind) {
   if (design_chain(t.design)) return kind == BULK_ERASE ? 33 : 60;
-  if (design_iceberg(t.design)) return kind != BULK_INSERT ? 12 : design_tags(t.design) ? 15 : 18;
+  if (design_iceberg(t.design)) return design_tags(t.design) ? 10 : 12;
   if (design_tags(t.design)) return t.B < 32 ? 13 : 10;
   if (t.kv_bits == 32) return t.B < 16 ? 21 : 16;
+  if (t.B >= 16) return 25;
   if (kind == BULK_ERASE) return 32;
   return kind == BULK_INSERT && t.nbh * t.B <= 1u << 13 ? 25 : 29;
 }
@@ -545,15 +545,16 @@ bool bulk_plan(const BulkShape& t, uint64_t n, BulkKind kind, uint64_t call, Bul
   // there are backyard buckets, as in a plain call, where such choices are spread
   // over the call's time.  All at once they meet equal fills and take the first choice
   // (ICEBERG, 2^20 slots filled to 0.9 in one call: 2.91 lines per query with all tiles,
-  // 2.95 with the limit, 2.96 plain; 202, 308 and 582 us).  Calls of few blocks take
-  // twice as many tiles: with the limit they were slower than plain calls in nearly full
-  // tables (2^15 slots from 0.75 to 0.95: 149 us plain, 188 with the limit, 156 so),
-  // and their choices are few (the standard deviation of the backyard's fills is 0.95 in all three).
+  // 2.95 with the limit, 2.96 plain; 202, 308 and 582 us).  Calls of few blocks, or of few
+  // operations for the table, take twice as many tiles (per 32 slots of a bucket): with the limit they were
+  // slower than plain calls in nearly full tables (2^15 slots from 0.75 to 0.95: 149 us plain,
+  // 188 with the limit, 156 so), and a few choices at a time leave the backyard as even
+  // (the standard deviation of its fills is 0.95 in all three).
   p->slow_tiles = BULK_THREADS;
   if (!erase && design_iceberg(t.design)) {
     const uint64_t blocks = std::min<uint64_t>(p->parts, BULK_RESIDENT);
-    const bool idle = member ? call < BULK_FILL * 256 : p->parts < BULK_FILL;
-    p->slow_tiles = (uint32_t)std::min<uint64_t>(BULK_THREADS, t.backs * (idle ? 2 : 1) / blocks + 1);
+    const bool few = (member ? call < BULK_FILL * 256 : p->parts < BULK_FILL) || n * 4 < nbh * B;
+    p->slow_tiles = (uint32_t)std::min<uint64_t>(BULK_THREADS, t.backs * (few ? B / 16 : 1) / blocks + 1);
   }
   p->sub = 0;
   p->levels = p->parts <= (uint32_t)BULK_BINS ? 1 : 2;

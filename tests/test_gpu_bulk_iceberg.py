@@ -19,11 +19,12 @@ def fills(t):
     return occ[int(0.84 * t.num_buckets):]  # the front yard is the first 83%
 
 
-@pytest.mark.parametrize("design,bits,tile", [("ICEBERG", 64, 8), ("ICEBERG_M", 64, 4), ("ICEBERG", 32, 8)])
-@pytest.mark.parametrize("cap,start", [(1 << 15, 0.75), (1 << 18, 0.75), (1 << 18, 0.0), (1 << 20, 0.0)])
+@pytest.mark.parametrize("design,bits,bucket,tile", [("ICEBERG", 64, 32, 8), ("ICEBERG_M", 64, 32, 4), ("ICEBERG", 32, 32, 8),
+                                                     ("ICEBERG_M", 64, 64, 8)])
+@pytest.mark.parametrize("cap,start", [(1 << 15, 0.75), (1 << 18, 0.75), (1 << 18, 0.0), (1 << 20, 0.8), (1 << 20, 0.0)])
 @pytest.mark.parametrize("erased", [False, True])
-def test_near_full_placement_equals_plain_calls(design, bits, tile, cap, start, erased, monkeypatch):
-    t = hw.Table(cap, design, kv_bits=bits, bucket=32, tile=tile)
+def test_near_full_placement_equals_plain_calls(design, bits, bucket, tile, cap, start, erased, monkeypatch):
+    t = hw.Table(cap, design, kv_bits=bits, bucket=bucket, tile=tile)
     grouped = hw.Table._scratch
     n, a, runs = int(0.95 * cap), int(start * cap), 12
     sd, full = {}, {}
@@ -50,6 +51,6 @@ def test_near_full_placement_equals_plain_calls(design, bits, tile, cap, start, 
             sd[how].append(fills(t).std())
     m = {x: np.mean(v) for x, v in sd.items()}
     se = np.hypot(*[np.std(v, ddof=1) / np.sqrt(runs) for v in sd.values()])
-    print("%s u%d 2^%d erased=%d: sd plain %.3f grouped %.3f +- %.3f, FULL %s" % (design, bits, cap.bit_length() - 1, erased, m["plain"], m["grouped"], se, full), flush=True)
+    print("%s u%d b%d 2^%d erased=%d: sd plain %.3f grouped %.3f +- %.3f, FULL %s" % (design, bits, bucket, cap.bit_length() - 1, erased, m["plain"], m["grouped"], se, full), flush=True)
     assert m["grouped"] <= m["plain"] + 5 * se + 0.02
     assert full["grouped"] <= full["plain"] + 5 * np.sqrt(full["plain"] + 1)

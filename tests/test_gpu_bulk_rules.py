@@ -17,9 +17,10 @@ LINES = [("DOUBLE", 64, 8, 8, "insert", 1 << 16, 0.27, 0.30), ("DOUBLE", 64, 8, 
          ("DOUBLE", 64, 8, 8, "erase", 1 << 14, 0.30, 0.33), ("DOUBLE", 32, 8, 4, "insert", 1 << 15, 0.19, 0.22),
          ("DOUBLE", 32, 16, 4, "insert", 1 << 15, 0.15, 0.17), ("DOUBLE_M", 64, 16, 4, "upsert", 1 << 16, 0.12, 0.14),
          ("DOUBLE_M", 64, 32, 4, "upsert", 1 << 16, 0.09, 0.11), ("P2_M", 64, 16, 4, "erase", 1 << 15, 0.12, 0.14),
-         ("P2_M", 64, 32, 4, "erase", 1 << 15, 0.09, 0.11), ("ICEBERG", 64, 32, 8, "insert", 1 << 17, 0.13, 0.16),
-         ("ICEBERG", 64, 32, 8, "upsert", 1 << 17, 0.08, 0.11), ("ICEBERG_M", 64, 32, 4, "insert", 1 << 17, 0.11, 0.13),
-         ("ICEBERG_M", 32, 32, 4, "insert", 1 << 17, 0.11, 0.13), ("CHAINING", 64, 0, 0, "erase", 1 << 15, 0.33, 0.39),
+         ("P2_M", 64, 32, 4, "erase", 1 << 15, 0.09, 0.11), ("ICEBERG", 64, 32, 8, "insert", 1 << 17, 0.08, 0.11),
+         ("P2", 64, 32, 8, "erase", 1 << 16, 0.23, 0.26), ("DOUBLE", 64, 16, 8, "erase", 1 << 16, 0.23, 0.26),
+         ("ICEBERG", 64, 32, 8, "upsert", 1 << 17, 0.08, 0.11), ("ICEBERG_M", 64, 32, 4, "insert", 1 << 17, 0.07, 0.09),
+         ("ICEBERG_M", 32, 32, 4, "upsert", 1 << 17, 0.07, 0.09), ("CHAINING", 64, 0, 0, "erase", 1 << 15, 0.33, 0.39),
          ("CHAINING", 64, 0, 0, "upsert", 1 << 15, 0.65, 0.71)]
 
 
