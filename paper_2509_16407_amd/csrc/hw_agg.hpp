@@ -111,7 +111,7 @@ __device__ void agg_window(const TableDev& tv, AggLds<typename C::K>& L, const t
   // from the front every wave would come to a hot key's bucket at the same time (4 M
   // operations on 1.6 M Zipf keys: 1.80 ms, 1.28 with this).
   const uint32_t first = (uint32_t)(((uint64_t)(uint32_t)(i0 / AGG_WIN * 0x9E3779B1u) * n_u) >> 32);
-  const uint32_t look = 8 * (n - n_u) >= n ? 1u : LOCK_SPINS;  // an eighth duplicates: a skewed batch
+  const uint32_t look = 16 * (n - n_u) >= n ? 1u : LOCK_SPINS;  // a sixteenth duplicates: a skewed batch
   for (uint32_t u = lane / C::T; u < n_u; u += 64 / C::T) {
     const uint32_t e = L.list[u + first < n_u ? u + first : u + first - n_u];
     const uint8_t st = Ops<C>::template upsert<LOOK>(tv, tile, L.key[e], L.val[e], combine, L.stat[e] ? (int)row : -1, look);
