@@ -1,6 +1,7 @@
 """What the compiler made of the kernels (CPU only): every device function is inlined
-(a call costs its kernel a stack in memory), and the persistent multi-table kernels
-have the registers and LDS for the occupancy that sizes their grids."""
+(a call costs its kernel a stack in memory), the persistent multi-table kernels
+have the registers and LDS for the occupancy that sizes their grids, and every 16-byte
+store of a slot is followed by the wait states that its data registers need."""
 import os
 import re
 import struct
@@ -37,10 +38,15 @@ def code_objects(so, tmp):
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
+def objects(tmp_path_factory):
+    return list(code_objects(hw.LIB_PATH, str(tmp_path_factory.mktemp("co"))))
+
+
+@pytest.fixture(scope="module")
+def kernels(objects):
     """name -> (VGPRs, LDS bytes) of every kernel, and the functions that are none."""
     res, other = {}, []
-    for co in code_objects(hw.LIB_PATH, str(tmp_path_factory.mktemp("co"))):
+    for co in objects:
         text = subprocess.run([LLVM + "llvm-readelf", "-W", "-s", "--notes", co], capture_output=True, text=True,
                               check=True).stdout
         funcs = set(re.findall(r" FUNC .* (\S+)$", text, re.M))
@@ -72,3 +78,17 @@ def test_multi_table_kernels_meet_their_occupancy(kernels):
         assert min(512 // (-(-vgprs // 8) * 8), 163840 // max(lds, 1)) >= waves, (name[:120], vgprs, lds)
         seen += 1
     assert seen >= 30
+
+
+def test_slot_stores_keep_their_registers(objects):
+    """A store of more than 8 bytes reads its data up to two states after it issues; written
+    in inline assembly it brings them itself, whatever instruction comes next."""
+    stores = 0
+    for co in objects:
+        text = subprocess.run([LLVM + "llvm-objdump", "-d", "--no-show-raw-insn", "--no-leading-addr", co],
+                              capture_output=True, text=True, check=True).stdout.split("\n")
+        for a, b in zip(text, text[1:]):
+            if "global_store_dwordx4" in a and "sc1" in a:
+                stores += 1
+                assert b.split()[:2] == ["s_nop", "1"], (a, b)
+    assert stores > 100
