@@ -761,12 +761,11 @@ def bench_batched(n_tables=4096, e_min=10, e_max=22, load=0.85, reps=3, tune_rep
     fills it to `load`.  Times one call over all tables (configuration
     autotuned per capacity class) against one plain launch per table and one call per
     table (same configurations; the calls group by bucket where that pays) and against one
-    persistent launch with a fixed default configuration.  A group of one configuration
-    runs grouped by bucket, in a few launches over all tables, a group of several on the
-    menu's persistent kernel; so when the classes chose different
-    configurations, one launch with the single configuration of least estimated
-    time (from the tuner's rates) is timed too, and the faster group is the
-    batched result.  Verifies every table's size and, on a sample of tables, every
+    persistent launch with a fixed default configuration.  The call over all tables
+    runs grouped by bucket, in a few launches per configuration; so when the classes
+    chose different configurations, one call with the single configuration of least
+    estimated time (from the tuner's rates) is timed too, and the faster group is
+    the batched result.  Verifies every table's size and, on a sample of tables, every
     key and value against the group-by sums computed directly with numpy."""
     import torch
     import paper_2509_16407_amd as hw
@@ -850,9 +849,9 @@ def bench_batched(n_tables=4096, e_min=10, e_max=22, load=0.85, reps=3, tune_rep
     one_cfg = lambda alls: one_config(alls, ops_of)
 
     def uniform_group(best_of, alls, flags):
-        """Per-class choices that differ put the group on the full menu's kernel; a
-        group of one configuration runs on that configuration's own.  Returns the
-        one-configuration alternative's (configuration, ms), or None when the
+        """Per-class choices that differ give each configuration launches of its own (or
+        put the group on the full menu's kernel).  Returns the one-configuration
+        alternative's (configuration, ms), or None when the
         per-class choices already agree."""
         if len({(v["design"], v["bucket"], v["tile"]) for v in best_of.values()}) == 1:
             return None
@@ -890,8 +889,7 @@ def bench_batched(n_tables=4096, e_min=10, e_max=22, load=0.85, reps=3, tune_rep
             log("batched (%s): the classes chose different configurations; one configuration (%s/b%d/t%d) for all "
                 "tables: %.2f Gops/s" % ((name,) + u[0] + (n_ops / u[1] / 1e6,)))
     # the group step of the tuning: of the two groups timed, the faster is the
-    # batched form's result (per-class choices on the menu's kernel, or one
-    # configuration on its own kernel)
+    # batched form's result
     best = lambda ms, u: (ms, "per-class configurations") if u is None or ms <= u[1] else \
         (u[1], "one configuration, %s/b%d/t%d" % u[0])
     ms_best, policy = best(ms_batched, uni)

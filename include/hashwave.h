@@ -424,9 +424,10 @@ int hwave_multi_upsert(hwave_multi* m, const uint64_t* h_offsets, const void* d_
                        hwave_combine combine, uint8_t* d_status, void* stream);
 
 /* The same with scratch memory, for bulk calls: as hwave_upsert_scratch, over all
- * tables of a group that share one configuration.  hwave_multi_scratch: the bytes the
- * call with these offsets can use, 0 where grouping does not pay.  Calls of more than
- * 2^27 operations run as several, each over a few of the tables, in the same memory. */
+ * tables of a group.  hwave_multi_scratch: the bytes the call with these offsets can
+ * use, 0 where grouping does not pay or a table's configuration has no grouped upsert.
+ * Calls of more than 2^27 operations run as several, each over a few of the tables, in
+ * the same memory; so do calls on tables of several configurations. */
 int hwave_multi_scratch(const hwave_multi* m, const uint64_t* h_offsets, hwave_combine combine, uint64_t* bytes);
 int hwave_multi_upsert_scratch(hwave_multi* m, const uint64_t* h_offsets, const void* d_keys, const void* d_vals,
                                hwave_combine combine, uint8_t* d_status, void* d_scratch, uint64_t scratch_bytes,

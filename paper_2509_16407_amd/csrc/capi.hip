@@ -445,6 +445,14 @@ constexpr uint32_t BULK_FILL = 512;
 // 87 us plain, 106 grouped; 51 104 / 110; 64 123 / 96).
 constexpr uint64_t BULK_MIN_MEMBER = 64;
 
+// Fewest operations per configuration for which a group of several is grouped.  Each
+// configuration's launches follow the others' (100 to 170 us a configuration however few
+// its operations), where one persistent launch runs all together.  Plain against grouped,
+// microseconds, 24 tables of 2^20 slots, present keys: nearly all operations on one
+// configuration of six, 0.65 M per configuration 773 / 995, 1.3 M 1656 / 1180; on one of four, 0.5 M
+// 516 / 667, 1.0 M 799 / 767; evenly on six, 1.26 M 1701 / 841.
+constexpr uint64_t GROUP_MIN_CONFIG = 1u << 20;
+
 // Room for a bin that receives `mean` operations on average: seven standard
 // deviations of a random spread; keys that are spread worse overflow into the
 // per-tile path.
@@ -1014,6 +1022,7 @@ struct hwave_multi {
   std::vector<uint64_t> table_bytes;  // footprint per table (queue placement)
   std::vector<BulkShape> shapes;      // per table, for grouped upserts
   std::vector<HomeMap> homes;
+  std::vector<uint32_t> order;        // the tables, those of one configuration together
   MultiTable* d_tables = nullptr;
   uint32_t* d_heads = nullptr;
   uint32_t* d_hot = nullptr;  // indices of the tables with hot-key accumulators the kernel fills
@@ -1102,6 +1111,9 @@ int hwave_multi_create(hwave_multi** out, hwave_table* const* tables, uint32_t n
     h[i].fill_words = locks_off / 16;
     h[i].zero_words = (t->bytes - locks_off) / 16;
   }
+  std::vector<uint32_t> order(n_tables);
+  for (uint32_t i = 0; i < n_tables; i++) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return h[a].cls < h[b].cls; });
   // every table on one configuration: that configuration's own kernel (its
   // entry in the 32-bit menu or in the 64-bit extended menu)
   int solo = (int)h[0].cls;
@@ -1120,6 +1132,7 @@ int hwave_multi_create(hwave_multi** out, hwave_table* const* tables, uint32_t n
   m->menu = menu;
   m->solo = solo;
   m->agg = false;
+  m->order = std::move(order);
   for (uint32_t i = 0; i < n_tables; i++) m->agg = m->agg || tables[i]->la.tv.aggregate;
   m->n_tables = n_tables;
   for (uint32_t i = 0; i < n_tables; i++) {
@@ -1276,10 +1289,11 @@ int hwave_multi_upsert(hwave_multi* m, const uint64_t* h_offsets, const void* d_
 
 namespace {
 
-// A group's upsert, grouped by bucket (hw_bulk.hpp), as runs of consecutive tables of at
-// most BULK_CHUNK operations (a larger table in pieces): one after another on the
-// stream, all in the same scratch memory.
+// A group's upsert, grouped by bucket (hw_bulk.hpp), as runs of tables of one
+// configuration and at most BULK_CHUNK operations (a larger table in pieces): one after
+// another on the stream, all in the same scratch memory.
 struct GroupRun {
+  const KernelSet* ks;
   size_t job;                 // first of its jobs
   uint32_t n;                 // jobs
   size_t list;                // offset of its list in the staging buffer: jobs, then `first`
@@ -1330,43 +1344,54 @@ bool group_run_layout(GroupPlan* g, GroupRun* r) {
 }
 
 // The runs of a call; false where one tile per operation is better: few operations, or
-// most of them in tables that get too few; and for tables of different configurations.
+// most of them in tables that get too few.
 //
 // One tile per operation against grouped, microseconds, 32-bit DOUBLE tables filled to
 // 0.85: 40 of 2^12 slots 360 / 65, 400 of 2^10 370 / 129, 4 of 2^20 658 / 216, 20 of 2^20 with 1.7
 // operations per slot 5125 / 1714; ICEBERG_M, 64-bit, 10 of 2^13 564 / 125, 20 of 2^20 5265 / 2041.
 bool group_plan(const hwave_multi* m, const uint64_t* offsets, int combine, GroupPlan* g) try {
-  if (m->menu != MENU_SOLO || !m->shapes[0].ks->group_upsert || (m->agg && combine != HWAVE_REPLACE)) return false;
+  if (m->agg && combine != HWAVE_REPLACE) return false;
   uint64_t total = 0, grouped = 0;
   for (uint32_t i = 0; i < m->n_tables; i++) {
     if (offsets[i + 1] < offsets[i]) return false;
     total += offsets[i + 1] - offsets[i];
   }
   if (total < BULK_MIN_OPS) return false;
-  uint64_t in_run = 0;
-  for (uint32_t i = 0; i < m->n_tables; i++) {
-    const uint64_t n = offsets[i + 1] - offsets[i];
-    if (n == 0) continue;
-    const uint64_t piece = bulk_piece(n);
-    BulkPlan plan{};
-    if (bulk_plan(m->shapes[i], piece, bulk_kind(combine), total, &plan)) grouped += n;
-    else plan = BulkPlan{};
-    for (uint64_t at = 0; at < n; at += piece) {
-      BulkJob j{};
-      j.plan = plan;
-      j.home = m->homes[i];
-      j.table = i;
-      j.n = (uint32_t)std::min(piece, n - at);
-      j.begin = offsets[i] + at;
-      if (g->runs.empty() || in_run + j.n > BULK_CHUNK) {
-        g->runs.push_back(GroupRun{g->jobs.size(), 0, 0, {}, {}});
-        in_run = 0;
+  auto ops = [&](uint32_t at) { return offsets[m->order[at] + 1] - offsets[m->order[at]]; };
+  uint64_t configs = 0;
+  for (uint32_t at = 0, end; at < m->n_tables; at = end) {  // tables of one configuration
+    const KernelSet* ks = m->shapes[m->order[at]].ks;
+    uint64_t call = 0, in_run = 0;
+    for (end = at; end < m->n_tables && m->shapes[m->order[end]].ks == ks; end++) call += ops(end);
+    if (call == 0) continue;
+    if (!ks->group_upsert) return false;
+    ++configs;
+    for (uint32_t k = at; k < end; k++) {
+      const uint32_t i = m->order[k];
+      const uint64_t n = ops(k);
+      if (n == 0) continue;
+      const uint64_t piece = bulk_piece(n);
+      BulkPlan plan{};
+      if (bulk_plan(m->shapes[i], piece, bulk_kind(combine), call, &plan)) grouped += n;
+      else plan = BulkPlan{};
+      for (uint64_t from = 0; from < n; from += piece) {
+        BulkJob j{};
+        j.plan = plan;
+        j.home = m->homes[i];
+        j.table = i;
+        j.n = (uint32_t)std::min(piece, n - from);
+        j.begin = offsets[i] + from;
+        if (in_run == 0 || in_run + j.n > BULK_CHUNK) {
+          g->runs.push_back(GroupRun{ks, g->jobs.size(), 0, 0, {}, {}});
+          in_run = 0;
+        }
+        in_run += j.n;
+        g->runs.back().n++;
+        g->jobs.push_back(j);
       }
-      in_run += j.n;
-      g->runs.back().n++;
-      g->jobs.push_back(j);
     }
   }
+  if (configs > 1 && total < configs * GROUP_MIN_CONFIG) return false;
   if (2 * grouped < total) return false;
   for (GroupRun& r : g->runs)
     if (!group_run_layout(g, &r)) return false;
@@ -1412,7 +1437,7 @@ int hwave_multi_upsert_scratch(hwave_multi* m, const uint64_t* h_offsets, const 
     r.args.g = BulkGroup{(const BulkJob*)scratch, (const uint32_t*)(scratch + r.first_at()), r.n, scratch};
     r.args.tables = m->d_tables;
     if (e == hipSuccess)
-      e = m->shapes[0].ks->group_upsert(r.args, &g.jobs[r.job], d_keys, d_vals, (int)combine, d_status, s);
+      e = r.ks->group_upsert(r.args, &g.jobs[r.job], d_keys, d_vals, (int)combine, d_status, s);
   }
   return e == hipSuccess ? HWAVE_OK : hip_fail(e);
 }

@@ -98,6 +98,48 @@ def test_group_in_runs_against_oracle(design, bits, bucket, tile, monkeypatch):
         dump_equal(t, om)
 
 
+MIX32 = [("DOUBLE", 16, 4), ("DOUBLE", 16, 8), ("DOUBLE", 64, 32)]
+MIX64 = [("DOUBLE_M", 32, 4), ("ICEBERG_M", 32, 4), ("CHAINING", 0, 0)]
+
+
+@pytest.mark.parametrize("bits,mix,grouped", [(32, MIX32, True), (64, MIX64, True), (64, [("P2_M", 32, 4)] + MIX64[1:], False)])
+def test_group_of_several_configurations_against_oracle(bits, mix, grouped):
+    """Tables of three configurations in turn, the first configuration with most of the
+    operations, the third with a table of a few; another one's tables get none.  Grouped from
+    2^20 operations per configuration on, where each configuration has a grouped upsert."""
+    cap = 1 << 20
+    each = 5 * cap // 8
+    ns = [each, 60000, 900, each, 0, 70000, each, 3, 0, each, 7, 0, 3 * cap - 4 * each - 130910]
+    tables = [hw.Table(cap if n > 60000 else 1 << 17, d, kv_bits=bits, bucket=b, tile=t)
+              for n, (d, b, t) in zip(ns, mix * 5)]
+    tables.append(hw.Table(1 << 10, "DOUBLE", kv_bits=bits, bucket=16, tile=8 if bits == 64 else 4))
+    ns.append(0)
+    m = hw.Multi(tables)
+    assert m.kernel()[0] != "solo" and sum(ns) == 3 * cap
+    ks, vs = [], []
+    for i, n in enumerate(ns):
+        seed = w.stream_seed(340 + i, bits)
+        pool = w.distinct_keys(seed, max(1, int(0.6 * n)), key_bits=bits)
+        ks.append(pool[w.uniform_below(seed + 1, 0, n, len(pool))] if n else np.empty(0, np.uint64))
+        vs.append(w.splitmix64(seed + 2, 0, n) & np.uint64(0xFFFFF))
+    offs = [0] + np.cumsum(ns).tolist()
+    keys, vals = np.concatenate(ks), np.concatenate(vs)
+    arr = (ctypes.c_uint64 * len(offs))(*offs)
+    assert (m._scratch(arr, len(keys), 0, None) is not None) == grouped
+    fewer = (ctypes.c_uint64 * len(offs))(0, *[x - 1 for x in offs[1:]])
+    assert m._scratch(fewer, len(keys) - 1, 0, None) is None
+    oms = [oracle.OracleMap(key_bits=bits) for _ in ns]
+    for _ in range(2):
+        st = u8(m.upsert(offs, dev(keys, bits), dev(vals, bits)))
+        for i, k in enumerate(ks):
+            if len(k):
+                ost = oms[i].upsert(k, vs[i])
+                for c in (hw.ST_DONE, hw.ST_EXISTED):
+                    assert per_key_counts(k, st[offs[i]: offs[i + 1]], c) == per_key_counts(k, ost, c), (i, c)
+    for t, om in zip(tables, oms):
+        dump_equal(t, om)
+
+
 def test_a_call_beyond_one_piece():
     """2^27 and 12,345 more operations on 10^8 keys, against sums worked out with torch:
     key i appears once, or twice if i < n - 10^8."""
