@@ -494,6 +494,10 @@ BulkKind bulk_kind(int combine) { return combine == HWAVE_KEEP ? BULK_INSERT : B
 //   tags, 32 slots:      inserts and upserts 0.10: 36 / 30 (2^15), 317 / 308 (2^25, present keys)
 //   tags, 16 slots:      0.10: DOUBLE_M present 27 / 30 (2^15), P2HT(M) erases of absent keys 21 / 23;
 //                        0.13: 32 / 29, 24 / 23
+//                        DOUBLE_M with 64-bit keys and tiles of up to 4, from 2^23 buckets on, where the tags are
+//                        twice the last-level cache: 32 slots, 2^28, 0.15: present 3758 / 3904, to
+//                        0.95 4855 / 5441; 0.20: 4950 / 4445, 6204 / 5653; 16 slots, 2^27, 0.15: to 0.95 2866 /
+//                        3152, 0.20: 3592 / 3204 (2^27 of 32 slots 0.15: 1983 / 1905, 2799 / 2666)
 //   32-bit keys:         8 slots 0.16: present 25 / 30 (2^15); 0.21: 30 / 29.  16 and more 0.16: 31 / 29
 //   64-bit, no tags:     8 slots 0.25: inserts to 0.95 69 / 84 (2^16), present 25 / 30 (2^14), but 2^13
 //                        fresh 32 / 27; 0.29: 73 / 73, 28 / 29.  Erases 0.25: absent 30 / 41, 0.29
@@ -504,7 +508,10 @@ BulkKind bulk_kind(int combine) { return combine == HWAVE_KEEP ? BULK_INSERT : B
 uint64_t bulk_min_percent(const BulkShape& t, BulkKind kind) {
   if (design_chain(t.design)) return kind == BULK_ERASE ? 33 : 60;
   if (design_iceberg(t.design)) return design_tags(t.design) ? 10 : 12;
-  if (design_tags(t.design)) return t.B < 32 ? 13 : 10;
+  if (design_tags(t.design)) {
+    if (kind != BULK_ERASE && t.kv_bits == 64 && t.ks->tile <= 4 && t.nbh >= 1u << 23) return 20;
+    return t.B < 32 ? 13 : 10;
+  }
   if (t.kv_bits == 32) return t.B < 16 ? 21 : 16;
   if (t.B >= 16) return 25;
   if (kind == BULK_ERASE) return 32;

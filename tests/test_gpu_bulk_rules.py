@@ -21,10 +21,14 @@ LINES = [("DOUBLE", 64, 8, 8, "insert", 1 << 16, 0.27, 0.30), ("DOUBLE", 64, 8, 
          ("P2", 64, 32, 8, "erase", 1 << 16, 0.23, 0.26), ("DOUBLE", 64, 16, 8, "erase", 1 << 16, 0.23, 0.26),
          ("ICEBERG", 64, 32, 8, "upsert", 1 << 17, 0.08, 0.11), ("ICEBERG_M", 64, 32, 4, "insert", 1 << 17, 0.07, 0.09),
          ("ICEBERG_M", 32, 32, 4, "upsert", 1 << 17, 0.07, 0.09), ("CHAINING", 64, 0, 0, "erase", 1 << 15, 0.33, 0.39),
-         ("CHAINING", 64, 0, 0, "upsert", 1 << 15, 0.65, 0.71)]
+         ("CHAINING", 64, 0, 0, "upsert", 1 << 15, 0.65, 0.71),
+         # from 2^23 buckets on
+         ("DOUBLE_M", 64, 32, 4, "insert", 1 << 28, 0.19, 0.21), ("DOUBLE_M", 64, 16, 4, "upsert", 1 << 27, 0.19, 0.21),
+         ("DOUBLE_M", 64, 32, 4, "upsert", 1 << 27, 0.09, 0.11), ("DOUBLE_M", 64, 32, 4, "erase", 1 << 28, 0.09, 0.11),
+         ("DOUBLE_M", 64, 32, 8, "insert", 1 << 28, 0.09, 0.11), ("DOUBLE_M", 32, 32, 4, "insert", 1 << 28, 0.09, 0.11)]
 
 
-@pytest.mark.parametrize("design,bits,bucket,tile,kind,cap,below,above", LINES, ids=["%s-u%d-b%d-%s" % (c[0], c[1], c[2], c[4]) for c in LINES])
+@pytest.mark.parametrize("design,bits,bucket,tile,kind,cap,below,above", LINES, ids=["%s-u%d-b%d-t%d-%s-%d" % c[:6] for c in LINES])
 def test_least_share_of_the_slots(design, bits, bucket, tile, kind, cap, below, above):
     t = hw.Table(cap, design, kv_bits=bits, bucket=bucket, tile=tile)
     grouped = lambda per: t._scratch(hw.OPS[kind], int(per * cap), hw.COMBINES["keep" if kind == "insert" else "sum"], None) is not None
